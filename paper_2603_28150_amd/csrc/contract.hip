@@ -6,446 +6,503 @@
 // H^ is real and identical for all frequencies of one symmetry class, so the
 // library keeps one slab per class in two layouts, [l][n] for A and [n][l] for
 // A^T.  Both products then have the same shape: the summed index i runs over
-// slab rows, the kept index j runs along a row, and one workgroup (or, for
-// long rows, two, each taking half of every row) streams one slab exactly once
-// while applying it to every member frequency of its work item (up to eight).  Streaming the slab is the whole cost (it is >95 % of the bytes
-// an apply moves), so the kernel is built around 16-byte non-temporal loads
-// of whole rows: lanes of a row group cover one row, row groups take
-// interleaved rows, and a short LDS tree adds the row-group partial sums at
-// the end.  Accumulation is float32 for every storage type.
+// slab rows, the kept index j runs along a row, and the slab serves every
+// (member frequency, object) pair of its work item.  For one object streaming
+// the slab is the whole cost (>95 % of the bytes an apply moves).
+//
+// The product runs on the float32 matrix instruction v_mfma_f32_16x16x4_f32:
+// its 16 rows are the real and imaginary parts of 8 pairs, its 16 columns are
+// outputs, 4 slab rows are summed per instruction, all in float32.  A wave owns
+// a tile of 16 VEC outputs (VEC values per 16-byte load) and streams its slab
+// rows straight into the operand registers, VEC instructions per load: no
+// barrier and no sum across lanes, so that a wave only ever waits for its own
+// loads, and no vector arithmetic beside the matrix instructions (a load costs
+// one issue slot: scalar block base plus a fixed lane offset).
+//
+// Bound by HBM at full size, by latency below: the vector kernel this replaced
+// (one workgroup per slab, spectra in LDS, an LDS tree over the row groups)
+// took, per launch of A / A^T: 32 x 32 x 16 x 64, 9.7 / 11 us, now 4 / 4 (the
+// tree was six levels deep); 128 x 128 x 96 x 384, 53 / 57, now 50 / 47;
+// 202 x 202 x 37 x 256 on 432 x 432, 171 / 221, now 144 / 157; 256 x 256 x
+// 128 x 512, 307 / 287, now 300 / 277 (5.9 TB/s); with bf16 slabs 195 / 200,
+// now 179 / 164 (groups of 8 members read a slab once that two items of 4
+// read twice).  FISTA's Gram products of 4 objects (two to four pairs of
+// columns per value loaded), per step: 256 x 256 x 128, 590 us, now 484;
+// 128 x 128 x 96, 121, now 95.
+#include <algorithm>
 #include <type_traits>
 
-#include "dft.hpp"
+#include "contract_slab.hpp"
 #include "pat_internal.hpp"
 
 namespace pat {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+typedef float v4f8 __attribute__((ext_vector_type(4), aligned(8)));  // two complex values, 8-byte aligned
 
-constexpr int kRowParts = 2;  // workgroups per item and object for long rows
+// orders a wave's own LDS accesses (no other wave touches them)
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
 
-template <typename HT> struct Slab;
+// workgroup barrier that orders LDS accesses only (global loads stay in flight)
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+// bytes of a staged pair: the rows of four lane groups and eight pairs that a
+// wave reads together fall into different banks
+__host__ __device__ __forceinline__ int xl_stride(int ni) { return (ni * 8 + 255) / 256 * 256 + 64; }
 
-template <> struct Slab<float> {
-  static constexpr int VEC = 4;
-  typedef v4f raw_t;
-  __device__ static __forceinline__ float get(const raw_t& r, int v) { return r[v]; }
-};
+// Rows are taken in blocks of 8: lane group c = lane / 16 holds rows 2c and
+// 2c + 1 of a block (two 16-byte slab loads), so that one 16-byte load brings
+// both rows' spectrum values of a pair.  Two register buffers of U blocks
+// keep up to 4 U slab loads of a wave in flight.
 
-struct bf16_t { unsigned short bits; };
-struct f16_t { unsigned short bits; };
-
-template <> struct Slab<bf16_t> {
-  static constexpr int VEC = 8;
-  typedef v4u raw_t;
-  __device__ static __forceinline__ float get(const raw_t& r, int v) {
-    const unsigned w = r[v >> 1];
-    const unsigned b = (v & 1) ? (w & 0xFFFF0000u) : (w << 16);
-    return __uint_as_float(b);
-  }
-};
-
-template <> struct Slab<f16_t> {
-  static constexpr int VEC = 8;
-  typedef v4u raw_t;
-  __device__ static __forceinline__ float get(const raw_t& r, int v) {
-    const unsigned w = r[v >> 1];
-    const unsigned short h = (v & 1) ? (unsigned short)(w >> 16) : (unsigned short)(w & 0xFFFFu);
-    _Float16 x;
-    __builtin_memcpy(&x, &h, 2);
-    return (float)x;
-  }
-};
-
-// One work item: GG active member slots (GG <= G, the slot count of the
-// spectrum rows).  Uniform per workgroup.
-// float32 slabs with rows of one chunk per lane: two rows per register
-// buffer instead of four, so that the kernel fits 128 registers and four
-// waves per SIMD (measured faster on short rows, neutral on long ones)
-template <typename HT, int JPT>
-constexpr bool kLowRegs = std::is_same<HT, float>::value && JPT == 1;
-
-template <typename HT, int G, int GG, int JPT>
-__device__ __forceinline__ void contract_item(const ContractArgs& a, int lr_log2, int t, int b, int j0,
-                                              int njl, const int (&kg)[G], float4* smem_raw) {
+// One wave: outputs [tile * 16 VEC, ...) of the CT * 8 pairs from pg0 on,
+// summed over the wave's share (kpart of KP) of the row blocks; the shares
+// are added in a fixed order by share 0, which stores the result.  np: pairs
+// of the group (members times objects).
+//
+// Short rows (at most half or a quarter of a tile) with few pairs leave lanes
+// and instruction rows idle: then S = 2 or 4 sets of 16/S lanes take different
+// row blocks of the slab, set i's pairs in the instruction rows 16 i/S .., and
+// only the diagonal (set, set) part of the product is used and summed.
+//
+// XL: the pairs' spectra go through LDS first, whole runs of a row per load
+// (where they are long and come from memory, reading them piecewise between
+// the slab loads costs more than the barrier).  NT: non-temporal slab loads.
+// WT: output lines are written through.
+template <typename HT, int CT, int U, bool NT, bool WT, bool XL>
+__device__ __forceinline__ void stream_tile(const ContractArgs& a, int row0, int slab_id, int tile, int kpart, int KP,
+                                            int pg0, int np, float* red) {
   typedef Slab<HT> SL;
   typedef typename SL::raw_t raw_t;
   constexpr int VEC = SL::VEC;
-  constexpr int U = kLowRegs<HT, JPT> ? 2 : 4 / JPT;  // rows per register buffer
-  constexpr int NS = JPT * VEC * GG * 2;    // accumulators per thread
-  float2* xin = reinterpret_cast<float2*>(smem_raw);
-  float* red = reinterpret_cast<float*>(smem_raw);
-  const int tid = threadIdx.x;
-  const int Lr = 1 << lr_log2, R = 256 >> lr_log2;
-  const int lr = tid & (Lr - 1), rg = tid >> lr_log2;
+  constexpr unsigned ESZ = sizeof(HT);
+  const int lane = threadIdx.x & 63;
+  const int c = lane >> 4, l16 = lane & 15;
+  int ls = 0;  // log2 S
+  if (CT == 1 && !XL && a.nj <= 8 * VEC) ls = (a.nj <= 4 * VEC && np - pg0 <= 2) ? 2 : np - pg0 <= 4 ? 1 : 0;
+  const int pmask = (8 >> ls) - 1;  // pairs of a set of lanes
+  const int set = l16 >> (4 - ls);
+  const int lb = 3 + ls;         // log2 rows per block
+  const int nfull = a.ni >> lb;  // whole blocks; a partial one is the last share's
+  const int b0 = nfull * kpart / KP, b1 = nfull * (kpart + 1) / KP;
 
-  // this workgroup's part of the rows: elements j0 .. j0 + njl - 1
-  const HT* slab = reinterpret_cast<const HT*>(a.slab) + (size_t)a.item_slab[t] * a.slab_elems + j0;
-  const int nchunks = (njl + VEC - 1) / VEC;
-  bool cl[JPT];
-  const HT* colp[JPT];
+  // Addresses: a wave-uniform base that advances by blocks (scalar
+  // arithmetic) plus a fixed 32-bit byte offset per lane, so that a load costs
+  // no vector instruction besides itself (the launcher checks the range).
+  constexpr int tn = 16 * VEC;  // outputs of a tile
+  const int n = tile * tn + VEC * (l16 & ((16 >> ls) - 1));  // first output of this lane
+  const unsigned col = min(n, a.s_row - VEC);  // clamped: always a valid address
+  const char* hb = reinterpret_cast<const char*>(reinterpret_cast<const HT*>(a.slab) + (size_t)slab_id * a.slab_elems);
+  const unsigned rl = 8 * set + 2 * c;  // this lane's first row in a block
+  const unsigned hv[2] = {(rl * a.s_row + col) * ESZ, ((rl + 1) * a.s_row + col) * ESZ};
+  const unsigned hstep = (unsigned)(a.s_row << lb) * ESZ;
+  const int xstep = 8 << lb;
+  // spectrum rows of this lane's pairs (a pair past the end reads pair pg0's)
+  const char* xb = reinterpret_cast<const char*>(a.in + (size_t)row0 * a.in_rs);
+  unsigned xv[CT];
 #pragma unroll
-  for (int jj = 0; jj < JPT; ++jj) {
-    const int ch = lr + jj * Lr;
-    cl[jj] = ch < nchunks;
-    colp[jj] = slab + (size_t)min(ch, nchunks - 1) * VEC;  // clamped: always a valid address
+  for (int m = 0; m < CT; ++m) {
+    const int pr = pg0 + 8 * m + ((l16 >> 1) & pmask);
+    const int p = pr < np ? pr : pg0;
+    const int g = a.B == 1 ? p : p / a.B, b = p - g * a.B;
+    xv[m] = (unsigned)(g * a.in_rs + b * a.ni) * 8u + rl * 8u;
+  }
+  const bool im = lane & 1;
+  unsigned xl[XL ? CT : 1];  // the same in LDS
+  const int xstride = xl_stride(a.ni);  // bytes per pair
+  if constexpr (XL) {
+#pragma unroll
+    for (int m = 0; m < CT; ++m) {
+      const int pl = 8 * m + ((l16 >> 1) & pmask);
+      xl[m] = (pg0 + pl < np ? pl : 0) * xstride + rl * 8;
+    }
   }
 
-  // Rows in flight: the loads of the next U rows are issued before the FMAs
-  // of the current ones (two register buffers), so that every wave keeps
-  // memory requests outstanding while it computes.  Loads are unconditional
-  // (rows and chunks clamped into the slab, the value zeroed by a select) so
-  // that no branch hides them from the wait counter.
-  auto load_rows = [&](raw_t (&raw)[U][JPT], int i0) {
+  struct Buf {
+    raw_t h[U][2];
+    v4f x[U][CT];
+    float2 sc[VEC == 8 ? U : 1];
+  };
+  // keeps a 32-bit offset next to its load (widened in advance, it would take
+  // two registers and a 64-bit addition per load)
+  auto here = [](unsigned o) {
+    asm("" : "+v"(o));
+    return o;
+  };
+  auto slab_load = [&](const char* q) {
+    const raw_t* p = reinterpret_cast<const raw_t*>(q);
+    return NT ? __builtin_nontemporal_load(p) : *p;
+  };
+  // Loads of row blocks b .. b + U - 1, unconditional (past the last whole
+  // block it is read again and not used) so that no branch hides them from
+  // the wait counter.
+  auto load = [&](Buf& o, int b) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int i = i0 + u * R;
-      const int ic = min(i, a.ni - 1);
+      const int bb = min(b + u, nfull - 1);
+      const char* ph = hb + (unsigned)bb * hstep;
+      const char* px = xb + (size_t)bb * xstep;
 #pragma unroll
-      for (int jj = 0; jj < JPT; ++jj) {
-        const raw_t v = __builtin_nontemporal_load(
-            reinterpret_cast<const raw_t*>(colp[jj] + (size_t)ic * a.s_row));
-        raw[u][jj] = (i < a.ni && cl[jj]) ? v : raw_t(0);
+      for (int s = 0; s < 2; ++s) o.h[u][s] = slab_load(ph + here(hv[s]));
+      if constexpr (!XL) {
+#pragma unroll
+        for (int m = 0; m < CT; ++m) o.x[u][m] = *reinterpret_cast<const v4f8*>(px + here(xv[m]));
+      }
+      if constexpr (VEC == 8)
+        o.sc[u] = a.in_scale ? *reinterpret_cast<const float2*>(a.in_scale + ((size_t)bb << lb) + rl)
+                             : make_float2(1.f, 1.f);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // the products that follow stay behind these loads
+  };
+  // spectrum values of row blocks b .. b + U - 1 from LDS
+  auto load_x = [&](Buf& o, int b) {
+    if constexpr (XL) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int m = 0; m < CT; ++m)
+          o.x[u][m] = *reinterpret_cast<const v4f*>(reinterpret_cast<const char*>(red) + xl[m] + min(b + u, nfull - 1) * xstep);
+    }
+  };
+  // The matrix instruction adds its four products to the accumulator one after
+  // the other: sums of 8 or 16 rows are kept apart (part) and added to the
+  // total, which shortens the chain of roundings from the share's length to
+  // that of a group plus the number of groups.
+  v4f acc[CT][VEC], part[CT][VEC];
+#pragma unroll
+  for (int m = 0; m < CT; ++m)
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) acc[m][v] = part[m][v] = v4f(0.f);
+  auto flush = [&]() {
+#pragma unroll
+    for (int m = 0; m < CT; ++m)
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) {
+        acc[m][v] += part[m][v];
+        part[m][v] = v4f(0.f);
+      }
+  };
+  auto mma_block = [&](const raw_t (&h)[2], const v4f (&x)[CT], float2 sc) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      float xs[CT];
+#pragma unroll
+      for (int m = 0; m < CT; ++m) {
+        xs[m] = im ? x[m][2 * s + 1] : x[m][2 * s];
+        if constexpr (VEC == 8) xs[m] *= s ? sc.y : sc.x;
+      }
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) {
+        const float hval = SL::get(h[s], v);
+#pragma unroll
+        for (int m = 0; m < CT; ++m)
+          part[m][v] = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[m], hval, part[m][v], 0, 0, 0);
       }
     }
   };
-  raw_t ra[U][JPT], rb[U][JPT];
-  load_rows(ra, rg);  // the first rows travel while the member vectors are staged
-
-  // member input vectors -> LDS xin[i][g], with the optional per-row scale;
-  // 16-byte loads along each member row when the row length is even
-  if ((a.ni & 1) == 0) {
-    // batches of kStage loads per thread, all issued before their LDS stores
-    // (one memory latency per batch instead of one per load); consecutive
-    // lanes take consecutive members of one k pair, so that the LDS stores
-    // are contiguous (the loads still cover whole 128-byte lines per wave)
-    constexpr int kStage = 8;
-    const int h = a.ni >> 1;
-    const int total = GG * h;
-    for (int base = tid; base < total; base += 256 * kStage) {
-      float4 v[kStage];
-      float2 sv[kStage];  // the per-row scales of the pair, loaded with it
-#pragma unroll
-      for (int q = 0; q < kStage; ++q) {
-        const int idx = base + q * 256;
-        v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-        sv[q] = make_float2(1.f, 1.f);
-        if (idx < total) {
-          const int g = idx % GG, i = 2 * (idx / GG);
-          int k = -1;
-#pragma unroll
-          for (int gg = 0; gg < GG; ++gg) k = (gg == g) ? kg[gg] : k;
-          if (k >= 0)
-            v[q] = *reinterpret_cast<const float4*>(a.in + (size_t)(t * G + g) * a.in_rs + (size_t)b * a.ni + i);
-          if (a.in_scale) sv[q] = *reinterpret_cast<const float2*>(a.in_scale + i);
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < kStage; ++q) {
-        const int idx = base + q * 256;
-        if (idx >= total) break;
-        const int g = idx % GG, i = 2 * (idx / GG);
-        float4 w = v[q];
-        if (a.in_scale) w = make_float4(w.x * sv[q].x, w.y * sv[q].x, w.z * sv[q].y, w.w * sv[q].y);
-        xin[i * GG + g] = make_float2(w.x, w.y);
-        xin[(i + 1) * GG + g] = make_float2(w.z, w.w);
-      }
-    }
-  } else {
-    for (int idx = tid; idx < a.ni * GG; idx += 256) {
-      const int i = idx / GG, g = idx % GG;
-      int k = -1;
-#pragma unroll
-      for (int gg = 0; gg < GG; ++gg) k = (gg == g) ? kg[gg] : k;
-      float2 v = make_float2(0.f, 0.f);
-      if (k >= 0) {
-        v = a.in[(size_t)(t * G + g) * a.in_rs + (size_t)b * a.ni + i];
-        if (a.in_scale) v = cscale(v, a.in_scale[i]);
-      }
-      xin[idx] = v;
-    }
-  }
-  __syncthreads();
-
-  float acc[NS];
-#pragma unroll
-  for (int s = 0; s < NS; ++s) acc[s] = 0.f;
-
-  auto fma_rows = [&](const raw_t (&raw)[U][JPT], int i0) {
+  auto mma = [&](const Buf& o, int b) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int i = i0 + u * R;
-      if (i >= a.ni) break;
-      float2 xv[GG];
-#pragma unroll
-      for (int g = 0; g < GG; ++g) xv[g] = xin[i * GG + g];
-#pragma unroll
-      for (int jj = 0; jj < JPT; ++jj) {
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-          const float h = SL::get(raw[u][jj], v);
-#pragma unroll
-          for (int g = 0; g < GG; ++g) {
-            float* p = &acc[((jj * VEC + v) * GG + g) * 2];
-            p[0] = fmaf(h, xv[g].x, p[0]);
-            p[1] = fmaf(h, xv[g].y, p[1]);
-          }
-        }
-      }
+      if (b + u >= b1) break;
+      mma_block(o.h[u], o.x[u], o.sc[VEC == 8 ? u : 0]);
+      if (u % 2 == 1 || (VEC == 4 && CT == 1 && U == 2)) flush();
     }
+    __builtin_amdgcn_sched_barrier(0);
   };
-  for (int i0 = rg; i0 < a.ni; i0 += 2 * R * U) {
-    load_rows(rb, i0 + R * U);
-    fma_rows(ra, i0);
-    if (i0 + R * U >= a.ni) break;
-    load_rows(ra, i0 + 2 * R * U);
-    fma_rows(rb, i0 + R * U);
-  }
 
-  // add the partial sums of the R row groups (fixed order: deterministic)
-  for (int half = R >> 1; half >= 1; half >>= 1) {
-    __syncthreads();
-    const int span = half * Lr;
-    if (rg >= half && rg < 2 * half) {
-      const int w = (rg - half) * Lr + lr;
+  // the rows after the last whole block: loaded first (clamped into the slab
+  // and, in pairs, into the spectrum row), multiplied last
+  const bool tail = (nfull << lb) < a.ni && kpart == KP - 1;
+  const int r0 = (nfull << lb) + rl;
+  raw_t th[2];
+  v4f tx[CT];
+  float2 tsc = make_float2(1.f, 1.f);
+  if (tail) {
+    const int x0 = min(r0, (a.ni - 1) & ~1);
 #pragma unroll
-      for (int s = 0; s < NS; ++s) red[s * span + w] = acc[s];
+    for (int s = 0; s < 2; ++s)
+      th[s] = slab_load(hb + (unsigned)(min(r0 + s, a.ni - 1) * a.s_row + col) * ESZ);
+#pragma unroll
+    for (int m = 0; m < CT; ++m)
+      tx[m] = *reinterpret_cast<const v4f8*>(xb + (xv[m] - rl * 8u) + (unsigned)x0 * 8u);
+    if (VEC == 8 && a.in_scale)
+      tsc = make_float2(a.in_scale[min(r0, a.ni - 1)], a.in_scale[min(r0 + 1, a.ni - 1)]);
+  }
+  Buf ba, bb;
+  if (b0 < b1) load(ba, b0);
+  if constexpr (XL) {
+    // the pairs' spectra into LDS, whole runs of a row per wave instruction
+    constexpr int kRun = 4;
+    const int nw = blockDim.x >> 6, wv = threadIdx.x >> 6, h = (a.ni + 1) >> 1;
+    const int npl = min(8 * CT, np - pg0);
+    for (int p = wv; p < npl; p += nw) {
+      const int pr = pg0 + p;
+      const int g = a.B == 1 ? pr : pr / a.B, ob = pr - g * a.B;
+      const char* src = xb + (size_t)(g * a.in_rs + ob * a.ni) * 8;
+      char* dst = reinterpret_cast<char*>(red) + p * xstride;
+      for (int q0 = lane; q0 < h; q0 += 64 * kRun) {
+        v4f v[kRun];
+#pragma unroll
+        for (int r = 0; r < kRun; ++r) v[r] = *reinterpret_cast<const v4f8*>(src + min(q0 + 64 * r, h - 1) * 16);
+#pragma unroll
+        for (int r = 0; r < kRun; ++r)
+          if (q0 + 64 * r < h) *reinterpret_cast<v4f*>(dst + (q0 + 64 * r) * 16) = v[r];
+      }
     }
-    __syncthreads();
-    if (rg < half) {
-      const int w = rg * Lr + lr;
-#pragma unroll
-      for (int s = 0; s < NS; ++s) acc[s] += red[s * span + w];
+    lds_barrier();
+  }
+  if (b0 < b1) {
+    // the loads of the next blocks go out before the products of the current ones
+    int b = b0;
+    load_x(ba, b);
+    for (; b + 2 * U < b1; b += 2 * U) {
+      load(bb, b + U);
+      load_x(bb, b + U);
+      mma(ba, b);
+      load(ba, b + 2 * U);
+      load_x(ba, b + 2 * U);
+      mma(bb, b + U);
+      if (U == 1) flush();
+    }
+    if (b + U < b1) {
+      load(bb, b + U);
+      load_x(bb, b + U);
+      mma(ba, b);
+      mma(bb, b + U);
+    } else {
+      mma(ba, b);
     }
   }
-
-  // float32, whole 16-byte pairs per lane and nothing to subtract: row group
-  // 0 stores its sums directly (each lane four consecutive outputs per
-  // member, the lanes of a member row contiguous), without a pass through
-  // LDS (A and A^T 1.5 % faster; the 16-bit kernels, eight outputs per lane,
-  // measured 4 % slower that way and keep the pass through LDS)
-  if (std::is_same<HT, float>::value && a.out_sub == nullptr && (a.nj & 1) == 0 && njl % VEC == 0) {
-    if (rg != 0) return;
-    if (a.out_scale) {
-      // per-row output scales, all loaded before the first use and applied
-      // here, so that no load is outstanding at the stores below
-      float scv[JPT][VEC];
+  if (tail) {
 #pragma unroll
-      for (int jj = 0; jj < JPT; ++jj)
+    for (int s = 0; s < 2; ++s)
+      if (r0 + s >= a.ni) {  // past the end: zeros
+        th[s] = raw_t(0);
+#pragma unroll
+        for (int m = 0; m < CT; ++m) tx[m][2 * s] = tx[m][2 * s + 1] = 0.f;
+      }
+    if (U > 1) flush();
+    mma_block(th, tx, tsc);
+  }
+  flush();
+
+  const int w = threadIdx.x >> 6;
+  if (XL) lds_barrier();  // every wave is done with the staged spectra
+  if (KP > 1) {  // shares 1 .. KP-1 pass their sums through LDS (workgroup-uniform)
+    constexpr int NA = CT * VEC * 4;
+    float* mine = red + (size_t)w * NA * 64 + lane;
+    if (kpart > 0) {
+#pragma unroll
+      for (int m = 0; m < CT; ++m)
 #pragma unroll
         for (int v = 0; v < VEC; ++v)
-          scv[jj][v] = a.out_scale[j0 + min((lr + jj * Lr) * VEC + v, njl - 1)];
 #pragma unroll
-      for (int jj = 0; jj < JPT; ++jj)
+          for (int r = 0; r < 4; ++r) mine[((m * VEC + v) * 4 + r) * 64] = acc[m][v][r];
+    }
+    lds_barrier();
+    if (kpart > 0) return;
+    for (int p = 1; p < KP; ++p) {
+#pragma unroll
+      for (int m = 0; m < CT; ++m)
 #pragma unroll
         for (int v = 0; v < VEC; ++v)
 #pragma unroll
-          for (int g = 0; g < GG; ++g) {
-            float* q = &acc[((jj * VEC + v) * GG + g) * 2];
-            q[0] *= scv[jj][v];
-            q[1] *= scv[jj][v];
-          }
+          for (int r = 0; r < 4; ++r)
+            acc[m][v][r] += mine[(size_t)p * NA * 64 + ((m * VEC + v) * 4 + r) * 64];
     }
-#pragma unroll
-    for (int jj = 0; jj < JPT; ++jj) {
-      const int cj = (lr + jj * Lr) * VEC;
-      if (cj >= njl) continue;
-#pragma unroll
-      for (int g = 0; g < GG; ++g) {
-        if (kg[g] < 0) continue;
-        v4f* dst = reinterpret_cast<v4f*>(a.out + (size_t)(t * G + g) * a.out_rs + (size_t)b * a.nj + j0 + cj);
-#pragma unroll
-        for (int v = 0; v < VEC; v += 2) {
-          const float* q0 = &acc[((jj * VEC + v) * GG + g) * 2];
-          const float* q1 = &acc[((jj * VEC + v + 1) * GG + g) * 2];
-          __builtin_nontemporal_store(v4f{q0[0], q0[1], q1[0], q1[1]}, dst + v / 2);
-        }
-      }
-    }
-    return;
   }
 
-  // stage the member rows in LDS, then store each row contiguously (whole
-  // cache lines per store instruction)
-  __syncthreads();
-  float2* ob = reinterpret_cast<float2*>(smem_raw);
-  if (rg == 0) {
-    // per-row output scales: every load issued before the first is used
-    float scv[JPT][VEC];
+  // Accumulator row r of lane group c holds a part of pair 2c + r/2 (re, im), at output n + v for instruction v.  The tile goes
+  // through the wave's own part of LDS so that each store instruction writes
+  // whole runs of a spectrum row instead of half of every 32 bytes.
+  constexpr int NU = VEC;                       // 16-byte units per lane
+  constexpr int lu = VEC == 8 ? 6 : 5;          // log2 units of a row (tn / 2)
+  float* tr = red + (size_t)w * (KP > 1 ? CT : 1) * VEC * 256;
+  const size_t obase = (size_t)row0 * a.out_rs;
+  const auto orow = __builtin_amdgcn_make_buffer_rsrc(a.out + obase, (short)0, 8 * a.out_rs * 8, 0x00020000);
+  float osc[VEC];
 #pragma unroll
-    for (int jj = 0; jj < JPT; ++jj)
+  for (int v = 0; v < VEC; ++v) osc[v] = a.out_scale ? a.out_scale[min(n + v, a.nj - 1)] : 1.f;
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) {
-        const int j = (lr + jj * Lr) * VEC + v;
-        scv[jj][v] = a.out_scale ? a.out_scale[j0 + min(j, njl - 1)] : 1.f;
-      }
+  for (int m = 0; m < CT; ++m) {
+    if (pg0 + 8 * m >= np) break;
+    if ((2 * c) >> (3 - ls) == set) {  // S > 1: only the set's own pairs
 #pragma unroll
-    for (int jj = 0; jj < JPT; ++jj) {
+      for (int e = 0; e < 2; ++e)
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) {
-        const int j = (lr + jj * Lr) * VEC + v;
-        if (j >= njl) continue;
-        const float sc = scv[jj][v];
+        for (int v = 0; v < VEC; v += 2)
+          *reinterpret_cast<v4f*>(tr + (2 * c + e) * 2 * tn + 2 * (n - tile * tn + v)) =
+              v4f{acc[m][v][2 * e] * osc[v], acc[m][v][2 * e + 1] * osc[v],
+                  acc[m][v + 1][2 * e] * osc[v + 1], acc[m][v + 1][2 * e + 1] * osc[v + 1]};
+    }
+    wave_sync();
+    v4f d[NU];
+    size_t off[NU];
+    int left[NU];  // outputs of the unit to store: 2, 1 or (<= 0) none
 #pragma unroll
-        for (int g = 0; g < GG; ++g) {
-          const float* p = &acc[((jj * VEC + v) * GG + g) * 2];
-          ob[g * njl + j] = make_float2(p[0] * sc, p[1] * sc);
-        }
+    for (int j = 0; j < NU; ++j) {
+      const int idx = j * 64 + lane, q = idx & ((1 << lu) - 1);
+      const int pr = pg0 + 8 * m + (idx >> lu);
+      const int g = a.B == 1 ? pr : pr / a.B, ob = pr - g * a.B;
+      const int nq = tile * tn + 2 * q;
+      off[j] = (size_t)(row0 + g) * a.out_rs + (size_t)ob * a.nj + nq;
+      left[j] = pr < np ? a.nj - nq : 0;
+      d[j] = v4f(0.f);
+      if (left[j] > 0) {
+        d[j] = *reinterpret_cast<const v4f*>(tr + 4 * idx);
+        for (int k = 1; k < (1 << ls); ++k) d[j] += *reinterpret_cast<const v4f*>(tr + 4 * idx + k * (8 >> ls) * 2 * tn);
       }
     }
-  }
-  __syncthreads();
-  if ((njl & 1) == 0 && (a.nj & 1) == 0) {
-    // two complex values (16 bytes) per store, non-temporal: the rows are
-    // not read again by this kernel
-    // groups of kOut elements per thread: the values of a group (and the
-    // subtracted ones) are all read into separate registers before its
-    // first store; a load issued after a store, or a register rewritten
-    // while a store still reads it, waits for that store on the in-order
-    // memory counter
-    constexpr int kOut = 2;
-    const int h = njl >> 1;
-    for (int e0 = tid; e0 < GG * h; e0 += 256 * kOut) {
-      float4 val[kOut], sub[kOut];
-      bool ok[kOut];
+    if (a.out_sub) {
+      v4f sub[NU];
 #pragma unroll
-      for (int q = 0; q < kOut; ++q) {
-        const int e = e0 + q * 256;
-        const int g = e / h, j = 2 * (e - g * h);
-        int k = -1;
-#pragma unroll
-        for (int gg = 0; gg < GG; ++gg) k = (gg == g) ? kg[gg] : k;
-        ok[q] = e < GG * h && k >= 0;
-        sub[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-        val[q] = sub[q];
-        if (ok[q]) {
-          val[q] = *reinterpret_cast<const float4*>(ob + g * njl + j);
-          if (a.out_sub)
-            sub[q] = *reinterpret_cast<const float4*>(a.out_sub + (size_t)(t * G + g) * a.out_rs +
-                                                      (size_t)b * a.nj + j0 + j);
+      for (int j = 0; j < NU; ++j) {
+        sub[j] = v4f(0.f);
+        if (left[j] >= 2) {
+          sub[j] = *reinterpret_cast<const v4f8*>(a.out_sub + off[j]);
+        } else if (left[j] == 1) {
+          const float2 w1 = a.out_sub[off[j]];
+          sub[j][0] = w1.x;
+          sub[j][1] = w1.y;
         }
       }
-      // differences on straight-line code (the empty asm keeps them out of
-      // the conditional stores, where each store would wait again)
-      v4f d[kOut];
 #pragma unroll
-      for (int q = 0; q < kOut; ++q) {
-        d[q] = v4f{val[q].x - sub[q].x, val[q].y - sub[q].y, val[q].z - sub[q].z, val[q].w - sub[q].w};
-        asm volatile("" : "+v"(d[q]));
-      }
+      for (int j = 0; j < NU; ++j) d[j] -= sub[j];
+    }
 #pragma unroll
-      for (int q = 0; q < kOut; ++q) {
-        const int e = e0 + q * 256;
-        const int g = e / h, j = 2 * (e - g * h);
-        if (ok[q]) {
-          const size_t o = (size_t)(t * G + g) * a.out_rs + (size_t)b * a.nj + j0 + j;
-          __builtin_nontemporal_store(d[q], reinterpret_cast<v4f*>(a.out + o));
+    for (int j = 0; j < NU; ++j) {
+      if (WT) {
+        if (left[j] > 0) {
+          v4u bits;
+          __builtin_memcpy(&bits, &d[j], 16);
+          __builtin_amdgcn_raw_buffer_store_b128(bits, orow, (int)((unsigned)(off[j] - obase) * 8u), 0, 16);  // sc1
         }
+      } else if (left[j] >= 2) {
+        __builtin_nontemporal_store((v4f8)d[j], reinterpret_cast<v4f8*>(a.out + off[j]));
+      } else if (left[j] == 1) {
+        a.out[off[j]] = make_float2(d[j][0], d[j][1]);
       }
     }
-  } else {
-    for (int e = tid; e < GG * njl; e += 256) {
-      const int g = e / njl, j = e - g * njl;
-      int k = -1;
-#pragma unroll
-      for (int gg = 0; gg < GG; ++gg) k = (gg == g) ? kg[gg] : k;
-      if (k >= 0) {
-        const size_t o = (size_t)(t * G + g) * a.out_rs + (size_t)b * a.nj + j0 + j;
-        a.out[o] = a.out_sub ? csub(ob[e], a.out_sub[o]) : ob[e];
-      }
-    }
+    wave_sync();
   }
 }
 
-// Workgroups -> (item t, object b, row part).  One object: JS workgroups per
-// item, each streaming 1/JS of every slab row (shorter workgroups, a shorter
-// tail); a batch: one workgroup per item and object.  Workgroups are dealt to
-// the eight XCDs round-robin by index, so the units (item, part or object),
-// in item order, are cut into eight contiguous ranges, one per XCD, each
-// taken in order: the B objects of an item, and the items a large class is
-// split into (adjacent, reading the same slab), run on one XCD at about the
-// same time, and every read of a slab after the first comes from that XCD's
-// L2 instead of HBM.
-__device__ __forceinline__ bool item_of_block(int nitem, int B, int JS, int& t, int& b, int& part) {
-  const int per_item = B == 1 ? JS : B;
-  const int units = nitem * per_item;
+// Workgroup = TW tiles x KP row shares of one (item, tile group, pair group).
+// Workgroups are dealt to the eight XCDs round-robin by index, so the units,
+// in item order, are cut into eight contiguous ranges, one per XCD, each taken
+// in order: the pair groups of an item, and the items a large class is split
+// into (adjacent, reading the same slab), run on one XCD at about the same
+// time, and every read of a slab after the first comes from that XCD's L2
+// instead of HBM.
+// Slabs that come round again before this much else has been read stay in the
+// memory-side cache (256 MB) with plain loads; a larger working set streams,
+// and non-temporal loads stream faster (7.1 against 6.2 TB/s on a plain read
+// of 1.55 GB).  One A + one A^T: 128 x 128 x 64 x 256 (210 MB in both layouts)
+// 108 us plain, 111 non-temporal; 128 x 128 x 96 x 384 (470 MB) 187 and 174.
+constexpr long long kCacheBytes = 256LL << 20;
+
+// Rows from which the spectra are staged in LDS (XL).  Shorter products gain
+// nothing from it (A^T of 128 x 128 x 64 x 256: 22.5 us direct, 25.4 staged);
+// at 229 and 512 rows the pair of applies is 2 % and 1 % faster staged
+// (192 x 192 x 100 x 229: 262.7 and 267.6 us; 256 x 256 x 128 x 512: 898 and
+// 908).  Rows of less than a tile are short runs of a slab with as many
+// spectrum bytes: staged, 202 x 202 x 37 x 256 (linear) took 640 instead of
+// 612 us.
+constexpr int kXlRows = 192;
+
+template <typename HT, int CT, int U, bool NT, bool WT, bool XL>
+__global__ __launch_bounds__(256, (CT > 1 ? 2 : 3)) void k_contract(ContractArgs a, int TW, int KP, int tgroups,
+                                                                     int pgroups, int ntile) {
+  extern __shared__ float red[];
+  const int units = a.ngroup * tgroups * pgroups;
   const int per_xcd = (units + 7) >> 3;
   const int u = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (u >= units) return false;
-  t = u / per_item;
-  const int rem = u - t * per_item;
-  part = B == 1 ? rem : 0;
-  b = B == 1 ? 0 : rem;
-  return true;
-}
-
-template <typename HT, int G, int JPT>
-__global__ __launch_bounds__(256, (kLowRegs<HT, JPT> ? 4 : 1)) void k_contract(ContractArgs a, int lr_log2, int B, int JS, int chpart) {
-  extern __shared__ float4 smem_raw[];
-  int t, b, part;
-  if (!item_of_block(a.nitem, B, JS, t, b, part)) return;  // whole workgroup: padding of the grid
-  constexpr int VEC = Slab<HT>::VEC;
-  const int j0 = part * chpart * VEC;
-  const int njl = min(a.nj - j0, chpart * VEC);
-  int kg[G];
-#pragma unroll
-  for (int g = 0; g < G; ++g) kg[g] = a.members[t * G + g];
-  if constexpr (G > 4) {
-    if (kg[4] < 0) {  // at most four members: the cheaper body
-      contract_item<HT, G, 4, JPT>(a, lr_log2, t, b, j0, njl, kg, smem_raw);
-      return;
-    }
+  if (u >= units) return;  // whole workgroup: padding of the grid
+  const int pg = u % pgroups, tg = (u / pgroups) % tgroups, t = u / (pgroups * tgroups);
+  const int4 grp = a.groups[t];  // first spectrum row, members, slab
+  const int np = grp.y * a.B, pg0 = pg * 8 * CT;
+  if (pg0 >= np) return;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kpart = w % KP, tile = min(tg * TW + w / KP, ntile);  // tile ntile: no outputs (idle wave)
+  if (!XL && KP == 1 && tile == ntile) return;
+  if constexpr (CT == 4) {  // few pairs left: the cheaper bodies
+    if (np - pg0 <= 8) return stream_tile<HT, 1, 2, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
+    if (np - pg0 <= 16) return stream_tile<HT, 2, 2, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
   }
-  contract_item<HT, G, G, JPT>(a, lr_log2, t, b, j0, njl, kg, smem_raw);
+  if constexpr (CT == 2) {
+    if (np - pg0 <= 8) return stream_tile<HT, 1, 2, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
+  }
+  stream_tile<HT, CT, U, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
 }
 
-template <typename HT, int G>
-static pat_status launch_t(const ContractArgs& a, int B, hipStream_t st) {
+template <typename HT, int CT, int U>
+static void launch_u(const ContractArgs& a, dim3 grid, int TW, int KP, int tgroups, int pgroups, int ntile, bool nt,
+                     bool xl, hipStream_t st) {
   constexpr int VEC = Slab<HT>::VEC;
-  // one object: rows of 128 or more 16-byte chunks are split over kRowParts
-  // workgroups per item (halves of 1 KB and more still stream well; shorter
-  // parts measured slower)
-  const int JS = (B == 1 && (a.nj + VEC - 1) / VEC >= 128) ? kRowParts : 1;
-  const int chpart = ((a.nj + VEC - 1) / VEC + JS - 1) / JS;  // 16-byte chunks per part
-  const int nchunks = chpart;
-  int lr_log2 = 0;
-  while ((1 << lr_log2) < nchunks && lr_log2 < 8) ++lr_log2;
-  const int Lr = 1 << lr_log2, R = 256 / Lr;
-  const int jpt = (nchunks + Lr - 1) / Lr;
-  if (jpt > 2) return fail(PAT_EUNSUPPORTED, "contraction row longer than 512 vectors");
-  const int ns = jpt * VEC * G * 2;
-  size_t red_bytes = R > 1 ? (size_t)(R / 2) * Lr * ns * sizeof(float) : 0;
-  size_t in_bytes = (size_t)a.ni * G * sizeof(float2);
-  size_t out_bytes = (size_t)chpart * VEC * G * sizeof(float2);
-  size_t lds = red_bytes > in_bytes ? red_bytes : in_bytes;
-  lds = lds > out_bytes ? lds : out_bytes;
-  if (lds > 160 * 1024) return fail(PAT_EUNSUPPORTED, "contraction input vector does not fit in LDS");
-  const long long nblk = ((long long)a.nitem * (B == 1 ? JS : B) + 7) / 8 * 8;
+  // Written-through lines (whole 128-byte lines only: parts of lines made the
+  // launch up to twice as slow) where little is written per slab byte: mixing
+  // writes into the slab stream costs more than their bytes (1.55 GB read in
+  // 0.23 ms without stores, 0.29 with 135 MB of them), written through a
+  // little less: FISTA's Gram products 157 against 160 us a step at
+  // 256 x 256 x 128.  A's spectra stay cached for the transform that follows.
+  const bool wt = a.nj % 16 == 0 && (a.gram || a.ni >= 256);
+  const dim3 block(64 * TW * KP);
+  const size_t lds = std::max((size_t)TW * KP * (KP > 1 ? CT : 1) * VEC * 256 * sizeof(float),
+                              xl ? (size_t)8 * CT * xl_stride(a.ni) : 0);
+  auto go = [&](auto kernel) { kernel<<<grid, block, lds, st>>>(a, TW, KP, tgroups, pgroups, ntile); };
+  if constexpr (CT == 1) {
+    if (xl && wt) return go(k_contract<HT, CT, U, true, true, true>);
+    if (xl) return go(k_contract<HT, CT, U, true, false, true>);
+  }
+  if (nt && wt) return go(k_contract<HT, CT, U, true, true, false>);
+  if (nt) return go(k_contract<HT, CT, U, true, false, false>);
+  if (wt) return go(k_contract<HT, CT, U, false, true, false>);
+  go(k_contract<HT, CT, U, false, false, false>);
+}
+
+template <typename HT, int CT>
+static pat_status launch_t(const ContractArgs& a, hipStream_t st) {
+  constexpr int VEC = Slab<HT>::VEC;
+  // four waves per workgroup: one per tile up to four tiles; with one or two
+  // tiles, four or two waves share the rows of each
+  constexpr int tn = 16 * VEC;
+  const int ntile = (a.nj + tn - 1) / tn;
+  const int tgroups = (ntile + 3) / 4, TW = (ntile + tgroups - 1) / tgroups;
+  const int KP = TW == 1 ? 4 : TW == 2 ? 2 : 1;
+  const int pgroups = (a.members * a.B + 8 * CT - 1) / (8 * CT);
+  const long long nblk = ((long long)a.ngroup * tgroups * pgroups + 7) / 8 * 8;
   if (nblk > 0x7fffffffLL) return fail(PAT_EUNSUPPORTED, "contraction grid too large");
-  dim3 grid((unsigned)nblk);
-  if (jpt == 1)
-    k_contract<HT, G, 1><<<grid, 256, lds, st>>>(a, lr_log2, B, JS, chpart);
+  const dim3 grid((unsigned)nblk);
+  const bool nt = a.reuse_bytes > kCacheBytes;
+  const bool xl = nt && a.members > 2 && a.ni >= kXlRows && a.nj >= 64 && (size_t)8 * xl_stride(a.ni) <= 64 * 1024;
+  const int share = (a.ni >> 3) / KP;  // row blocks of a wave
+  if (CT == 1 && VEC == 4 && share % 4 == 0)
+    launch_u<HT, CT, (CT == 1 && VEC == 4 ? 4 : 2)>(a, grid, TW, KP, tgroups, pgroups, ntile, nt, xl, st);
   else
-    k_contract<HT, G, 2><<<grid, 256, lds, st>>>(a, lr_log2, B, JS, chpart);
+    launch_u<HT, CT, (CT == 4 ? 1 : 2)>(a, grid, TW, KP, tgroups, pgroups, ntile, nt, xl, st);
   PAT_LAUNCHED("contraction");
   return PAT_OK;
 }
 
-pat_status contract(const ContractArgs& a, int hdtype, int G, int B, hipStream_t st) {
-  if (a.nitem == 0 || B == 0) return PAT_OK;
-  if (G == 8) {  // radial fold: float32 libraries only
-    if (hdtype == PAT_H_F32) return launch_t<float, 8>(a, B, st);
-    return fail(PAT_EUNSUPPORTED, "8-member work items need a float32 library");
-  }
-  if (G == 4) {
-    if (hdtype == PAT_H_F32) return launch_t<float, 4>(a, B, st);
-    if (hdtype == PAT_H_BF16) return launch_t<bf16_t, 4>(a, B, st);
-    return launch_t<f16_t, 4>(a, B, st);
-  }
-  if (hdtype == PAT_H_F32) return launch_t<float, 2>(a, B, st);
-  if (hdtype == PAT_H_BF16) return launch_t<bf16_t, 2>(a, B, st);
-  return launch_t<f16_t, 2>(a, B, st);
+pat_status contract(const ContractArgs& a, int hdtype, hipStream_t st) {
+  if (a.ngroup == 0 || a.B == 0) return PAT_OK;
+  if (a.slab_elems > (1LL << 28) || (long long)kGroup * a.in_rs > (1LL << 27) ||
+      (long long)kGroup * a.out_rs > (1LL << 27))
+    return fail(PAT_EUNSUPPORTED, "contraction slab or spectrum rows beyond 32-bit offsets");
+  // one object on the two-member fold: the vector units' kernel
+  if (a.members <= 2 && a.B == 1 && !a.out_sub && !a.gram) return contract_pair(a, hdtype, st);
+  if (hdtype == PAT_H_BF16) return launch_t<bf16_t, 1>(a, st);
+  if (hdtype == PAT_H_F16) return launch_t<f16_t, 1>(a, st);
+  const int pairs = a.members * a.B;
+  if (pairs <= 8) return launch_t<float, 1>(a, st);
+  if (pairs <= 16) return launch_t<float, 2>(a, st);
+  return launch_t<float, 4>(a, st);
 }
 
 }  // namespace pat

@@ -33,6 +33,8 @@ struct pat_op {
   int nrows;          // spectrum rows: nitem * G, item-major
   int32_t* members;   // [nitem][G]
   int32_t* item_slab; // [nitem]
+  int4* groups;       // [ngroup] members of a class by eights (contract's units)
+  int ngroup;
   int32_t* kclass;    // [nk] slab of frequency k
   int32_t* rowmap;    // [nk] spectrum row of frequency k
   int32_t* cls_freq;  // [nclass][2]
@@ -49,6 +51,7 @@ struct pat_op {
   pat::FftChirp chirp;  // chirp-z tables of axes that are not fast FFT sizes
   std::vector<float2> h_cz;  // their host copy: c and the kernel DFT, x then y
   std::vector<int32_t> h_members, h_kclass, h_cls_freq, h_rowmap, h_item_slab;
+  std::vector<int4> h_groups;
   std::vector<double> h_ir;  // sensor response taps folded into the library
 };
 
@@ -242,6 +245,7 @@ struct Classes {
   std::vector<int32_t> members;    // [nitem][G]
   std::vector<int32_t> kclass;     // [nk] slab of frequency k
   std::vector<int32_t> rowmap;     // [nk] spectrum row of frequency k
+  std::vector<int4> groups;        // members of a class by eights: first row, count, slab, 0
   int n() const { return (int)freq.size() / 2; }
   int nitem() const { return (int)item_slab.size(); }
 };
@@ -288,6 +292,10 @@ static Classes make_classes(const pat_geometry& g) {
   C.rowmap.assign(nk, -1);
   for (int gi = 0; gi < (int)groups.size(); ++gi) {
     const auto& mem = groups[gi];
+    // items are filled in order, so a class's rows are consecutive
+    const int row0 = C.nitem() * C.G;
+    for (int i0 = 0; i0 < (int)mem.size(); i0 += kGroup)
+      C.groups.push_back(make_int4(row0 + i0, std::min(kGroup, (int)mem.size() - i0), gi, 0));
     for (size_t i0 = 0; i0 < mem.size(); i0 += C.G) {
       const int item = (int)C.item_slab.size();
       C.item_slab.push_back(gi);
@@ -307,7 +315,7 @@ static Classes make_classes(const pat_geometry& g) {
 
 struct HLayout {
   size_t off_cz, bytes_cz;
-  size_t off_members, off_items, off_kclass, off_rowmap, off_freq, off_inv, off_amax, off_ir, off_A,
+  size_t off_members, off_items, off_groups, off_kclass, off_rowmap, off_freq, off_inv, off_amax, off_ir, off_A,
       off_T, off_Ar, off_Tr, off_G, off_X, total;
   size_t bytes_A, bytes_T, bytes_Ar, bytes_Tr, bytes_G, bytes_X;
   int sG_row;
@@ -345,6 +353,7 @@ static HLayout h_layout(const pat_geometry& g, const Classes& C) {
   size_t o = 0;
   L.off_members = o; o = align_up(o + (size_t)L.nitem * L.G * 4, 256);
   L.off_items = o;   o = align_up(o + (size_t)L.nitem * 4, 256);
+  L.off_groups = o;  o = align_up(o + C.groups.size() * sizeof(int4), 256);
   L.off_kclass = o;  o = align_up(o + (size_t)nk * 4, 256);
   L.off_rowmap = o;  o = align_up(o + (size_t)nk * 4, 256);
   L.off_freq = o;    o = align_up(o + (size_t)L.nclass * 8, 256);
@@ -458,12 +467,14 @@ static pat_status run_contract(pat_op* op, bool adjoint, const float2* in, float
                                hipStream_t st) {
   const pat_geometry& g = op->g;
   ContractArgs a;
-  a.members = op->members;
-  a.item_slab = op->item_slab;
+  a.groups = op->groups;
+  a.gram = false;
   a.in = in;
   a.out = out;
   a.out_sub = nullptr;
-  a.nitem = op->nitem;
+  a.ngroup = op->ngroup;
+  a.B = B;
+  a.members = op->G > 2 ? kGroup : 2;
   const float* sc = g.h_dtype == PAT_H_F32 ? nullptr : op->inv_scale;
   // one object: the VALU kernel on the row layouts streams the library at
   // the FP32 kernel's rate; batches go to the matrix cores (one slab read
@@ -535,9 +546,12 @@ static pat_status run_contract(pat_op* op, bool adjoint, const float2* in, float
     a.s_row = op->sT_row;
   }
   a.slab_elems = (long long)a.ni * a.s_row;
+  // A and A^T alternate in every loop that uses them: both layouts pass
+  // before one is read again
+  a.reuse_bytes = 2 * (long long)op->nclass * a.slab_elems * (g.h_dtype == PAT_H_F32 ? 4 : 2);
   a.in_rs = spec_stride(B * a.ni);
   a.out_rs = spec_stride(B * a.nj);
-  return contract(a, g.h_dtype, op->G, B, st);
+  return contract(a, g.h_dtype, st);
 }
 
 // Gram contraction: out = G z^ - sub per frequency, B spectra of nz slices
@@ -546,8 +560,8 @@ static pat_status run_gram(pat_op* op, const float2* in, float2* out, const floa
   const pat_geometry& g = op->g;
   ContractArgs a;
   a.slab = op->gram;
-  a.members = op->members;
-  a.item_slab = op->item_slab;
+  a.groups = op->groups;
+  a.gram = true;
   a.in = in;
   a.out = out;
   a.in_scale = nullptr;
@@ -557,10 +571,13 @@ static pat_status run_gram(pat_op* op, const float2* in, float2* out, const floa
   a.nj = g.nz;
   a.s_row = op->sG_row;
   a.slab_elems = (long long)g.nz * op->sG_row;
+  a.reuse_bytes = (long long)op->nclass * a.slab_elems * 4;  // iterations on the blocks alone
   a.in_rs = spec_stride(B * g.nz);
   a.out_rs = spec_stride(B * g.nz);
-  a.nitem = op->nitem;
-  return contract(a, PAT_H_F32, op->G, B, st);
+  a.ngroup = op->ngroup;
+  a.B = B;
+  a.members = op->G > 2 ? kGroup : 2;
+  return contract(a, PAT_H_F32, st);
 }
 
 // y = A x (- sub), B objects
@@ -728,6 +745,8 @@ pat_status pat_H_build(pat_ctx* ctx, const pat_geometry* geom, void* h_buf, size
   op->nrows = L.nitem * L.G;
   op->members = (int32_t*)(op->hbuf + L.off_members);
   op->item_slab = (int32_t*)(op->hbuf + L.off_items);
+  op->groups = (int4*)(op->hbuf + L.off_groups);
+  op->ngroup = (int)C.groups.size();
   op->kclass = (int32_t*)(op->hbuf + L.off_kclass);
   op->rowmap = (int32_t*)(op->hbuf + L.off_rowmap);
   op->cls_freq = (int32_t*)(op->hbuf + L.off_freq);
@@ -747,6 +766,7 @@ pat_status pat_H_build(pat_ctx* ctx, const pat_geometry* geom, void* h_buf, size
   op->h_cls_freq = std::move(C.freq);
   op->h_rowmap = std::move(C.rowmap);
   op->h_item_slab = std::move(C.item_slab);
+  op->h_groups = std::move(C.groups);
 
   auto bail = [&](pat_status s) {
     delete op;
@@ -769,6 +789,9 @@ pat_status pat_H_build(pat_ctx* ctx, const pat_geometry* geom, void* h_buf, size
     return bail(s);
   if ((s = hip_check(hipMemcpyAsync(op->item_slab, op->h_item_slab.data(), op->h_item_slab.size() * 4,
                                     hipMemcpyHostToDevice, st), "upload items")) != PAT_OK)
+    return bail(s);
+  if ((s = hip_check(hipMemcpyAsync(op->groups, op->h_groups.data(), op->h_groups.size() * sizeof(int4),
+                                    hipMemcpyHostToDevice, st), "upload groups")) != PAT_OK)
     return bail(s);
   double* d_ir = reinterpret_cast<double*>(op->hbuf + L.off_ir);
   if (geom->n_ir > 0 &&

@@ -69,25 +69,30 @@ pat_status fft2_c2r(const float2* X, float2* T, float* f, int fx, int fy, int nx
                     int sy, int S, float scale, const float* sub, const int32_t* rowmap,
                     const FftChirp& ch, hipStream_t st);
 
-// ------------------------------------------------------ contraction (VALU)
-// out[t*G+g][obj*nj + j] = sum_i slab_s[i][j] * in[t*G+g][obj*ni + i] (* scales)
-// for every work item t, its slab s = item_slab[t] and member slots g < G
-// (members[t*G+g] < 0: empty; filled slots come first).
+// ------------------------------------------------------ contraction (float32 matrix instructions)
+// out[r][obj*nj + j] = sum_i slab_s[i][j] * in[r][obj*ni + i] (* scales) for
+// the member rows r of every group of frequencies and objects obj < B.  A
+// group is up to kGroup members of one class: groups[t] = (first spectrum
+// row, members, slab s, 0), its rows consecutive.
+constexpr int kGroup = 8;
 struct ContractArgs {
   const void* slab;          // [nslab][ni][s_row] of the storage type
-  const int32_t* members;    // [nitem][G]
-  const int32_t* item_slab;  // [nitem]
-  const float2* in;          // [nitem*G][in_rs]  item-major spectrum rows
-  float2* out;               // [nitem*G][out_rs]
+  const int4* groups;        // [ngroup]
+  const float2* in;          // [rows][in_rs]  class-major spectrum rows
+  float2* out;               // [rows][out_rs]
   const float* in_scale;   // [ni] or null
   const float* out_scale;  // [nj] or null
   const float2* out_sub;   // null, or rows like out: out = result - out_sub
   int ni, nj, s_row;
   long long slab_elems;    // ni * s_row
   int in_rs, out_rs;
-  int nitem;
+  int ngroup, B, members;  // members: most of any group
+  bool gram;               // the slabs are Gram blocks
+  long long reuse_bytes;   // library bytes a caller's loop reads before it comes back to this launch's slabs
 };
-pat_status contract(const ContractArgs& a, int hdtype, int G, int B, hipStream_t st);
+pat_status contract(const ContractArgs& a, int hdtype, hipStream_t st);
+// the same for B = 1 and groups of at most two members (contract sends them here)
+pat_status contract_pair(const ContractArgs& a, int hdtype, hipStream_t st);
 
 // ------------------------------------------------------ contraction (MFMA)
 // out[c*G+g][b*N + n] = sum_k X[c*G+g][b*K + k] * S_c(k, n) for 16-bit slabs
