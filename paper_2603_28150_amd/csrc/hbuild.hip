@@ -33,9 +33,13 @@
 namespace pat {
 
 constexpr int kNT = 64;   // time samples per workgroup
-constexpr int kLP = 64;   // depths per pass (4 groups x 16)
+constexpr int kLP = 128;  // depths per pass
 constexpr int kQB = 32;   // q values per LDS chunk
+constexpr int kPS = 80;   // LDS row stride of a chunk: its four rows of a product fall into different banks
+constexpr int kTS = kLP + 1;  // LDS row stride of the finished tile
 constexpr int kMaxNq = 4096;
+
+typedef double v4d __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ int ceil_log2_d(double v) {
   int e;
@@ -64,11 +68,6 @@ __device__ __forceinline__ unsigned short to_f16(float f) {
   return b;
 }
 
-// MODE 0: per-depth max |H^| only, 1: write the slabs.  FIR: fold the sensor
-// response into the time axis.  The library is linear in the time factor
-// cos(n theta_q), so the filter acts on that factor: each q-chunk also
-// evaluates it at the n_ir - 1 earlier samples (zero before t = 0) and
-// filters in LDS before the depth sum.
 // Stepped time factor of class a.c0 + blockIdx.y for the wavenumbers
 // q = 0 .. nq/2 (one thread each): P^n(q) for n < nt, weighted by w_q / nq,
 // into ptab[(blockIdx.y * nt + n) * (nq/2 + 1) + q].
@@ -96,79 +95,145 @@ __global__ __launch_bounds__(256) void k_hstep(HBuildArgs a) {
   }
 }
 
+// LDS of k_hbuild: cos(2 pi r / nq), the time factors of a q chunk and (in
+// their place) the finished tile, then theta, cos theta and sin theta of every
+// q (closed form) and the sensor response with the unfiltered time factors
+struct BuildLds {
+  int o_p, o_th, o_raw, o_ir, total;
+  __host__ __device__ BuildLds(int nq, bool fir, bool step) {
+    const int qn = nq / 2 + 1;
+    o_p = nq * 8;
+    const int p = kQB * kPS * 8, t = kNT * kTS * 4;
+    o_th = o_p + (p > t ? p : t);
+    o_raw = o_th + (step ? 0 : 3 * qn * 8);
+    o_ir = o_raw + (fir ? kQB * (kNT + kMaxIr - 1) * 8 : 0);
+    total = o_ir + (fir ? kMaxIr * 8 : 0);
+  }
+};
+
+// MODE 0: per-depth max |H^| only, 1: write the slabs.  FIR: fold the sensor
+// response into the time axis.  The library is linear in the time factor
+// cos(n theta_q), so the filter acts on that factor: each q-chunk also
+// evaluates it at the n_ir - 1 earlier samples (zero before t = 0) and
+// filters in LDS before the depth sum.
+//
+// The depth sum is the product of the constant matrix cos(2 pi q l / nq) with
+// the class's time factors, on the float64 matrix instruction: workgroup =
+// (class, 64 samples), wave = half of the samples and every other 16 depths
+// of a pass of 128, so that a time factor is evaluated once per pass and a
+// cosine read from LDS serves two products.  Bound by the matrix rate (45 TF
+// measured for this instruction) and the evaluation of the time factors, one
+// sincos and seven rotations by theta for eight samples.  The vector form it
+// replaced (one multiply-add per cosine read, a cosine per sample, passes of
+// 64 depths) took 24.3 ms at 256 x 256 x 128 x 512 and 2.59 ms at
+// 128 x 128 x 96 x 384; now 5.4 and 0.51.
 template <int MODE, bool FIR, bool STEP>
-__global__ __launch_bounds__(256) void k_hbuild(HBuildArgs a) {
-  __shared__ double ctab[kMaxNq];
-  __shared__ double P[kQB * kNT];
-  __shared__ float tile[kNT * (kLP + 1)];
-  __shared__ double Praw[FIR ? kQB * (kNT + kMaxIr - 1) : 1];
-  __shared__ double irs[FIR ? kMaxIr : 1];
-  const int tid = threadIdx.x;
-  const int nl = tid & (kNT - 1), lg = tid >> 6;
+__global__ __launch_bounds__(256, 3) void k_hbuild(HBuildArgs a) {
+  extern __shared__ double hb_lds[];
+  const int nq = a.nq, Qn = nq / 2 + 1;
+  char* base = reinterpret_cast<char*>(hb_lds);
+  const BuildLds at(nq, FIR, STEP);
+  double* ctab = hb_lds;
+  double* P = reinterpret_cast<double*>(base + at.o_p);
+  float* tile = reinterpret_cast<float*>(base + at.o_p);
+  double* th = reinterpret_cast<double*>(base + at.o_th);
+  double* Praw = reinterpret_cast<double*>(base + at.o_raw);
+  double* irs = reinterpret_cast<double*>(base + at.o_ir);
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int li = lane & 15, lk = lane >> 4;
   const int c = a.c0 + blockIdx.y;
-  const int n = blockIdx.x * kNT + nl;
-  const double* rec = STEP ? a.ptab + (size_t)blockIdx.y * a.nt * (a.nq / 2 + 1) : nullptr;
-  const int nq = a.nq;
-  const int Qn = nq / 2 + 1;
+  const int n0 = blockIdx.x * kNT;
+  const double* rec = STEP ? a.ptab + (size_t)blockIdx.y * a.nt * Qn : nullptr;
   const double two_pi = 6.283185307179586476925286766559;
+  const double inv_nq = 1.0 / nq;
 
   for (int r = tid; r < nq; r += 256) ctab[r] = cos(two_pi * (double)r / (double)nq);
   if constexpr (FIR)
     for (int j = tid; j < a.n_ir; j += 256) irs[j] = a.ir[j];
+  if constexpr (!STEP) {
+    const double kx = two_pi * a.cls_freq[2 * c] / (a.nx * a.dx);
+    const double ky = two_pi * a.cls_freq[2 * c + 1] / (a.ny * a.dy);
+    const double kperp2 = kx * kx + ky * ky;
+    const double cdt = a.c * a.dt;
+    for (int q = tid; q < Qn; q += 256) {
+      const double kz = two_pi * q / (nq * a.dz);
+      const double theta = cdt * sqrt(kperp2 + kz * kz);
+      double sn, cs;
+      sincos(theta, &sn, &cs);
+      th[q] = theta;
+      th[Qn + q] = cs;
+      th[2 * Qn + q] = sn;
+    }
+  }
 
-  const int fx = a.cls_freq[2 * c], fy = a.cls_freq[2 * c + 1];
-  const double kx = two_pi * fx / (a.nx * a.dx);
-  const double ky = two_pi * fy / (a.ny * a.dy);
-  const double kperp2 = kx * kx + ky * ky;
-  const double cdt = a.c * a.dt;
-  const double inv_nq = 1.0 / nq;
+  // weighted time factors of samples ng .. ng + 7 at wavenumber q: one sincos,
+  // then rotations by theta (seven, a few 1e-16)
+  auto factors8 = [&](int q, int ng, double (&v)[8]) {
+    const double wq = (q == 0 || 2 * q == nq) ? inv_nq : 2.0 * inv_nq;
+    const double cs = th[Qn + q], sn = th[2 * Qn + q];
+    double C, S;
+    sincos((double)ng * th[q], &S, &C);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      v[j] = wq * C;
+      const double C1 = C * cs - S * sn;
+      S = S * cs + C * sn;
+      C = C1;
+    }
+  };
 
   for (int l0 = 0; l0 < a.nz; l0 += kLP) {
-    double acc[16];
-    int idx[16], stp[16];
+    // depth tile u of this wave: depths l0 + 16 (2u + w/2) + ..; samples
+    // 32 (w & 1) + 16 s + .. of the tile
+    const int nlt = (min(a.nz - l0, kLP) + 15) >> 4;
+    v4d acc[4][2];
+    int idx[4], stp[4];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      acc[u] = 0.0;
-      idx[u] = 0;
-      stp[u] = (l0 + lg + 4 * u) % nq;
+    for (int u = 0; u < 4; ++u) {
+      acc[u][0] = acc[u][1] = v4d{0.0, 0.0, 0.0, 0.0};
+      const int l = (l0 + 16 * (2 * u + (w >> 1)) + li) % nq;
+      idx[u] = (int)((long long)lk * l % nq);
+      stp[u] = (int)(4LL * l % nq);
     }
     for (int q0 = 0; q0 < Qn; q0 += kQB) {
       __syncthreads();
-      if constexpr (!FIR) {
+      if constexpr (!FIR && !STEP) {
+        const int qq = tid >> 3, nb = 8 * (tid & 7), q = q0 + qq;
+        double v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = 0.0;
+        if (q < Qn) factors8(q, n0 + nb, v);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) P[qq * kPS + nb + j] = n0 + nb + j < a.nt ? v[j] : 0.0;
+      } else if constexpr (!FIR) {
         for (int e = tid; e < kQB * kNT; e += 256) {
           const int qq = e / kNT, nn = e % kNT;
-          const int q = q0 + qq, ng = blockIdx.x * kNT + nn;
-          double v = 0.0;
-          if (q < Qn && ng < a.nt) {
-            if constexpr (STEP) {
-              v = rec[(size_t)ng * Qn + q];
-            } else {
-              const double kz = two_pi * q / (nq * a.dz);
-              const double theta = cdt * sqrt(kperp2 + kz * kz);
-              const double w = (q == 0 || 2 * q == nq) ? 1.0 : 2.0;
-              v = w * inv_nq * cos((double)ng * theta);
-            }
-          }
-          P[e] = v;
+          const int q = q0 + qq, ng = n0 + nn;
+          P[qq * kPS + nn] = (q < Qn && ng < a.nt) ? rec[(size_t)ng * Qn + q] : 0.0;
         }
       } else {
         const int L = a.n_ir, W = kNT + L - 1;
-        const int nbase = blockIdx.x * kNT - (L - 1);
-        for (int e = tid; e < kQB * W; e += 256) {
-          const int qq = e / W, nr = e % W;
-          const int q = q0 + qq, ng = nbase + nr;
-          double v = 0.0;
-          if (q < Qn && ng >= 0 && ng < a.nt) {
-            if constexpr (STEP) {
-              v = rec[(size_t)ng * Qn + q];
-            } else {
-              const double kz = two_pi * q / (nq * a.dz);
-              const double theta = cdt * sqrt(kperp2 + kz * kz);
-              const double w = (q == 0 || 2 * q == nq) ? 1.0 : 2.0;
-              v = w * inv_nq * cos((double)ng * theta);
+        const int nbase = n0 - (L - 1);
+        if constexpr (STEP) {
+          for (int e = tid; e < kQB * W; e += 256) {
+            const int qq = e / W, nr = e % W;
+            const int q = q0 + qq, ng = nbase + nr;
+            Praw[qq * W + nr] = (q < Qn && ng >= 0 && ng < a.nt) ? rec[(size_t)ng * Qn + q] : 0.0;
+          }
+        } else {
+          const int nblk = (W + 7) >> 3;
+          for (int e = tid; e < kQB * nblk; e += 256) {
+            const int qq = e / nblk, nb = 8 * (e - qq * nblk), q = q0 + qq;
+            double v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = 0.0;
+            if (q < Qn) factors8(q, nbase + nb, v);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              const int ng = nbase + nb + j;
+              if (nb + j < W) Praw[qq * W + nb + j] = (ng >= 0 && ng < a.nt) ? v[j] : 0.0;
             }
           }
-          Praw[qq * W + nr] = v;
         }
         __syncthreads();
         for (int e = tid; e < kQB * kNT; e += 256) {
@@ -176,55 +241,74 @@ __global__ __launch_bounds__(256) void k_hbuild(HBuildArgs a) {
           const double* pr = Praw + qq * W + nn + (L - 1);
           double v = 0.0;
           for (int j = 0; j < L; ++j) v = fma(irs[j], pr[-j], v);
-          P[e] = v;
+          P[qq * kPS + nn] = v;
         }
       }
       __syncthreads();
-      const int qe = (Qn - q0) < kQB ? (Qn - q0) : kQB;
-      for (int qq = 0; qq < qe; ++qq) {
-        const double p = P[qq * kNT + nl];
+      // four q per product; rows of P past the last q are zeros
+      const int steps = min(kQB / 4, (Qn - q0 + 3) >> 2);
+      for (int k = 0; k < steps; ++k) {
+        const double* pr = P + (4 * k + lk) * kPS + 32 * (w & 1) + li;
+        const double b0 = pr[0], b1 = pr[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-          acc[u] = fma(p, ctab[idx[u]], acc[u]);
+        for (int u = 0; u < 4; ++u) {
+          if (2 * u + (w >> 1) >= nlt) break;
+          const double x = ctab[idx[u]];
           idx[u] += stp[u];
           if (idx[u] >= nq) idx[u] -= nq;
+          acc[u][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, b0, acc[u][0], 0, 0, 0);
+          acc[u][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, b1, acc[u][1], 0, 0, 0);
         }
       }
     }
 
+    // accumulator register r of a lane: depth lk + 4 r, sample li of its tile
     if (MODE == 0) {
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int l = l0 + lg + 4 * u;
-        double m = (n < a.nt) ? fabs(acc[u]) : 0.0;
-        for (int off = 32; off >= 1; off >>= 1) m = fmax(m, __shfl_xor(m, off));
-        if (nl == 0 && l < a.nz)
-          atomicMax(&a.amax[l], (unsigned long long)__double_as_longlong(m));
-      }
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int l = l0 + 16 * (2 * u + (w >> 1)) + lk + 4 * r;
+          double m = 0.0;
+#pragma unroll
+          for (int s = 0; s < 2; ++s)
+            if (n0 + 32 * (w & 1) + 16 * s + li < a.nt) m = fmax(m, fabs(acc[u][s][r]));
+          for (int off = 8; off >= 1; off >>= 1) m = fmax(m, __shfl_xor(m, off));
+          if (li == 0 && l < a.nz) atomicMax(&a.amax[l], (unsigned long long)__double_as_longlong(m));
+        }
     } else {
-      // [l][n] rows: lanes along n, coalesced; the scaled values also go to
-      // the LDS tile for the transposed and the fragment layouts
+      // the scaled values through LDS (in place of the last chunk), so that
+      // every layout is written in runs
       __syncthreads();
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int ll = lg + 4 * u, l = l0 + ll;
-        float f = 0.f;
-        if (l < a.nz) f = (float)(acc[u] * depth_scale(a.amax, l, a.hdtype));
-        tile[nl * (kLP + 1) + ll] = f;
-        if (l < a.nz && n < a.nt) {
-          const size_t o = ((size_t)c * a.nz + l) * a.sA_row + n;
-          if (a.hdtype == PAT_H_F32) reinterpret_cast<float*>(a.rowA)[o] = f;
-          else if (a.hdtype == PAT_H_BF16) reinterpret_cast<unsigned short*>(a.rowA)[o] = to_bf16(f);
-          else reinterpret_cast<unsigned short*>(a.rowA)[o] = to_f16(f);
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int ll = 16 * (2 * u + (w >> 1)) + lk + 4 * r, l = l0 + ll;
+          const double sc = l < a.nz ? depth_scale(a.amax, l, a.hdtype) : 0.0;
+#pragma unroll
+          for (int s = 0; s < 2; ++s)
+            tile[(32 * (w & 1) + 16 * s + li) * kTS + ll] = (float)(acc[u][s][r] * sc);
         }
-      }
       __syncthreads();
-      // [n][l] rows: transpose through LDS so that lanes run along l
+      // [l][n] rows: lanes along n
+      const int nl = min(a.nz - l0, kLP);
+      for (int e = tid; e < kNT * nl; e += 256) {
+        const int ll = e / kNT, nn = e % kNT;
+        const int n = n0 + nn, l = l0 + ll;
+        if (n >= a.nt) continue;
+        const float f = tile[nn * kTS + ll];
+        const size_t o = ((size_t)c * a.nz + l) * a.sA_row + n;
+        if (a.hdtype == PAT_H_F32) reinterpret_cast<float*>(a.rowA)[o] = f;
+        else if (a.hdtype == PAT_H_BF16) reinterpret_cast<unsigned short*>(a.rowA)[o] = to_bf16(f);
+        else reinterpret_cast<unsigned short*>(a.rowA)[o] = to_f16(f);
+      }
+      // [n][l] rows: lanes along l
       for (int e = tid; e < kNT * kLP; e += 256) {
         const int nn = e / kLP, ll = e % kLP;
-        const int ng = blockIdx.x * kNT + nn, l = l0 + ll;
+        const int ng = n0 + nn, l = l0 + ll;
         if (ng >= a.nt || l >= a.nz) continue;
-        const float f = tile[nn * (kLP + 1) + ll];
+        const float f = tile[nn * kTS + ll];
         const size_t o = ((size_t)c * a.nt + ng) * a.sT_row + l;
         if (a.hdtype == PAT_H_F32) reinterpret_cast<float*>(a.rowT)[o] = f;
         else if (a.hdtype == PAT_H_BF16) reinterpret_cast<unsigned short*>(a.rowT)[o] = to_bf16(f);
@@ -232,21 +316,21 @@ __global__ __launch_bounds__(256) void k_hbuild(HBuildArgs a) {
       }
       if (a.hdtype != PAT_H_F32) {
         // 16-bit library: MFMA fragments for both directions, from the tile
-        const int n0 = blockIdx.x * kNT;
         for (int dir = 0; dir < 2; ++dir) {
           // dir 0: rows n, k = l (forward);  dir 1: rows l, k = n (adjoint)
           const int nt = dir == 0 ? a.ntA : a.ntT, ks = dir == 0 ? a.ksA : a.ksT;
           const int rt0 = (dir == 0 ? n0 : l0) / 32, kt0 = (dir == 0 ? l0 : n0) / 16;
+          const int kts = dir == 0 ? kLP / 16 : kNT / 16;  // k tiles of the LDS tile
           unsigned short* dst = reinterpret_cast<unsigned short*>(dir == 0 ? a.slabA : a.slabT);
-          for (int unit = tid; unit < 8 * 64; unit += 256) {
+          for (int unit = tid; unit < (kNT / 32) * (kLP / 16) * 64; unit += 256) {
             const int f = unit >> 6, L = unit & 63;
-            const int rt = f >> 2, kt = f & 3;
+            const int rt = f / kts, kt = f % kts;
             if (rt0 + rt >= nt || kt0 + kt >= ks) continue;
             const int r = rt * 32 + (L & 31), k = kt * 16 + 8 * (L >> 5);
             unsigned short v[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-              const float x = dir == 0 ? tile[r * (kLP + 1) + k + e] : tile[(k + e) * (kLP + 1) + r];
+              const float x = dir == 0 ? tile[r * kTS + k + e] : tile[(k + e) * kTS + r];
               v[e] = a.hdtype == PAT_H_BF16 ? to_bf16(x) : to_f16(x);
             }
             uint4 pk;
@@ -272,10 +356,11 @@ template <int MODE>
 static pat_status launch_depth_sum(const HBuildArgs& a, int ncls, hipStream_t st) {
   dim3 grid((a.nt + kNT - 1) / kNT, ncls);
   const bool fir = a.n_ir > 0, step = a.ptab != nullptr;
-  if (step && fir) k_hbuild<MODE, true, true><<<grid, 256, 0, st>>>(a);
-  else if (step) k_hbuild<MODE, false, true><<<grid, 256, 0, st>>>(a);
-  else if (fir) k_hbuild<MODE, true, false><<<grid, 256, 0, st>>>(a);
-  else k_hbuild<MODE, false, false><<<grid, 256, 0, st>>>(a);
+  const size_t lds = (size_t)BuildLds(a.nq, fir, step).total;
+  if (step && fir) k_hbuild<MODE, true, true><<<grid, 256, lds, st>>>(a);
+  else if (step) k_hbuild<MODE, false, true><<<grid, 256, lds, st>>>(a);
+  else if (fir) k_hbuild<MODE, true, false><<<grid, 256, lds, st>>>(a);
+  else k_hbuild<MODE, false, false><<<grid, 256, lds, st>>>(a);
   PAT_LAUNCHED(MODE == 0 ? "H build (max pass)" : "H build");
   return PAT_OK;
 }
@@ -354,68 +439,142 @@ pat_status hexport(const void* slabA, int hdtype, const int32_t* kclass, const f
 // is block diagonal in the transverse Fourier basis with these blocks, so the
 // gradient of the data term, A^T (A z - d) = A^T A z - A^T d (eq. 15), can be
 // formed per frequency from the spectrum of z alone.
-constexpr int kGN = 32;   // time samples per LDS chunk
+//
+// Blocks of 128 x 128 outputs on and above the diagonal (the rest is their
+// mirror image), in 16 x 16 tiles dealt to the four waves: the float64 matrix
+// instruction takes both operands in the same lane order (16 depths x 4
+// samples), read from one LDS chunk of the slab's rows.  Bound by the matrix
+// rate; the vector form it replaced (every block, 4 x 4 outputs per thread)
+// took 6.2 ms at 256 x 256 x 128 x 512, 1.17 at 128 x 128 x 96 x 384; now
+// 1.6 and 0.24.
+constexpr int kGN = 32;    // time samples per LDS chunk
+constexpr int kGB = 128;   // depths per block
+constexpr int kGS = kGN + 1;
+constexpr int kGP = 16;    // tile products per wave, at most (64 tiles, 4 waves)
 
-__device__ __forceinline__ float lib_value(const GramArgs& a, int s, int l, int n) {
-  if (a.hdtype == PAT_H_F32)
-    return reinterpret_cast<const float*>(a.slabA)[((size_t)s * a.nz + l) * a.sA_row + n];
-  const size_t o = ((((size_t)s * a.ntA + n / 32) * a.ksA + l / 16) * 64 + (n & 31) + 32 * ((l >> 3) & 1)) * 8 + (l & 7);
-  const unsigned short b = reinterpret_cast<const unsigned short*>(a.slabA)[o];
-  float f;
-  if (a.hdtype == PAT_H_BF16) {
-    f = __uint_as_float((unsigned)b << 16);
-  } else {
-    _Float16 h;
-    __builtin_memcpy(&h, &b, 2);
-    f = (float)h;
+// 4 consecutive library values of row l from sample n (a multiple of 4; rows
+// are padded with zeros to whole 16-byte units)
+__device__ __forceinline__ float4 lib_values(const GramArgs& a, int s, int l, int n) {
+  if (l >= a.nz || n >= a.sA_row) return make_float4(0.f, 0.f, 0.f, 0.f);
+  const size_t o = ((size_t)s * a.nz + l) * a.sA_row + n;
+  if (a.hdtype == PAT_H_F32) return *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(a.rowA) + o);
+  const ushort4 b = *reinterpret_cast<const ushort4*>(reinterpret_cast<const unsigned short*>(a.rowA) + o);
+  const unsigned short u[4] = {b.x, b.y, b.z, b.w};
+  float f[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if (a.hdtype == PAT_H_BF16) {
+      f[e] = __uint_as_float((unsigned)u[e] << 16);
+    } else {
+      _Float16 h;
+      __builtin_memcpy(&h, &u[e], 2);
+      f[e] = (float)h;
+    }
+    f[e] *= a.inv_scale[l];
   }
-  return f * a.inv_scale[l];
+  return make_float4(f[0], f[1], f[2], f[3]);
 }
 
-// workgroup = (slab, 64 x 64 output tile); thread = 4 x 4 outputs
-__global__ __launch_bounds__(256) void k_gram(GramArgs a) {
-  __shared__ double hi[64][kGN + 1], hj[64][kGN + 1];
-  const int s = blockIdx.z;
-  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-  const int tid = threadIdx.x;
-  const int ti = tid / 16, tj = tid % 16;
-  double acc[4][4] = {};
+__global__ __launch_bounds__(256, 2) void k_gram(GramArgs a, int nb) {
+  __shared__ float hi[kGB * kGS], hj[kGB * kGS];
+  const int nblk = nb * (nb + 1) / 2;
+  const int s = blockIdx.x / nblk, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+  int bi = 0, bj = blockIdx.x - s * nblk;  // block (bi, bj), bi <= bj, rows of nb, nb - 1, ... blocks
+  while (bj >= nb - bi) {
+    bj -= nb - bi;
+    ++bi;
+  }
+  bj += bi;
+  const int i0 = bi * kGB, j0 = bj * kGB;
+  const bool diag = bi == bj;
+  const int nti = (min(a.nz - i0, kGB) + 15) >> 4, ntj = (min(a.nz - j0, kGB) + 15) >> 4;
+  // tile products p = w, w + 4, ... of this wave: (ti, tj), ti <= tj on the diagonal
+  const int np = diag ? nti * (nti + 1) / 2 : nti * ntj;
+  int ti[kGP], tj[kGP];
+#pragma unroll
+  for (int m = 0; m < kGP; ++m) {
+    int p = w + 4 * m;
+    ti[m] = tj[m] = 0;
+    if (p < np) {
+      if (diag) {
+        while (p >= nti - ti[m]) {
+          p -= nti - ti[m];
+          ++ti[m];
+        }
+        tj[m] = ti[m] + p;
+      } else {
+        ti[m] = p / ntj;
+        tj[m] = p - ti[m] * ntj;
+      }
+    }
+    ti[m] = __builtin_amdgcn_readfirstlane(ti[m]);
+    tj[m] = __builtin_amdgcn_readfirstlane(tj[m]);
+  }
+  v4d acc[kGP];
+#pragma unroll
+  for (int m = 0; m < kGP; ++m) acc[m] = v4d{0.0, 0.0, 0.0, 0.0};
+  const float* hb = diag ? hi : hj;
+  const int lr = tid >> 3, lc = 4 * (tid & 7);  // rows lr + 32 r, samples lc .. lc + 3 of a chunk
+  float4 vi[4], vj[4];
+  auto fetch = [&](int n0) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      vi[r] = lib_values(a, s, i0 + lr + 32 * r, n0 + lc);
+      if (!diag) vj[r] = lib_values(a, s, j0 + lr + 32 * r, n0 + lc);
+    }
+  };
+  fetch(0);
   for (int n0 = 0; n0 < a.nt; n0 += kGN) {
     __syncthreads();
-    for (int e = tid; e < 64 * kGN; e += 256) {
-      const int r = e / kGN, nn = e % kGN;
-      const int n = n0 + nn;
-      hi[r][nn] = (i0 + r < a.nz && n < a.nt) ? (double)lib_value(a, s, i0 + r, n) : 0.0;
-      hj[r][nn] = (j0 + r < a.nz && n < a.nt) ? (double)lib_value(a, s, j0 + r, n) : 0.0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float* d = hi + (lr + 32 * r) * kGS + lc;
+      d[0] = vi[r].x;
+      d[1] = vi[r].y;
+      d[2] = vi[r].z;
+      d[3] = vi[r].w;
+      if (!diag) {
+        float* e = hj + (lr + 32 * r) * kGS + lc;
+        e[0] = vj[r].x;
+        e[1] = vj[r].y;
+        e[2] = vj[r].z;
+        e[3] = vj[r].w;
+      }
     }
     __syncthreads();
-    for (int nn = 0; nn < kGN; ++nn) {
-      double x[4], y[4];
+    if (n0 + kGN < a.nt) fetch(n0 + kGN);  // travels while this chunk is multiplied
+    for (int k = 0; k < kGN / 4; ++k) {
+      const int o = li * kGS + 4 * k + lk;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        x[u] = hi[ti + 16 * u][nn];
-        y[u] = hj[tj + 16 * u][nn];
+      for (int m = 0; m < kGP; ++m) {
+        if (w + 4 * m >= np) break;
+        const double x = hi[ti[m] * 16 * kGS + o], y = hb[tj[m] * 16 * kGS + o];
+        acc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, acc[m], 0, 0, 0);
       }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = fma(x[u], y[v], acc[u][v]);
     }
   }
+  float* g = a.gram + (size_t)s * a.nz * a.sG_row;
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int m = 0; m < kGP; ++m) {
+    if (w + 4 * m >= np) break;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = i0 + ti + 16 * u, j = j0 + tj + 16 * v;
-      if (i < a.nz && j < a.nz) a.gram[((size_t)s * a.nz + i) * a.sG_row + j] = (float)acc[u][v];
+    for (int r = 0; r < 4; ++r) {
+      const int i = i0 + 16 * ti[m] + lk + 4 * r, j = j0 + 16 * tj[m] + li;
+      if (i >= a.nz || j >= a.nz) continue;
+      const float v = (float)acc[m][r];
+      g[(size_t)i * a.sG_row + j] = v;
+      if (!diag || ti[m] != tj[m]) g[(size_t)j * a.sG_row + i] = v;
     }
+  }
 }
 
 pat_status gram_build(const GramArgs& a, hipStream_t st) {
   if (a.nslab == 0) return PAT_OK;
-  const int nb = (a.nz + 63) / 64;
-  dim3 grid(nb, nb, a.nslab);
-  k_gram<<<grid, 256, 0, st>>>(a);
+  const int nb = (a.nz + kGB - 1) / kGB;
+  const long long grid = (long long)a.nslab * (nb * (nb + 1) / 2);
+  if (grid > 0x7fffffffLL) return fail(PAT_EUNSUPPORTED, "Gram blocks: grid too large");
+  k_gram<<<dim3((unsigned)grid), 256, 0, st>>>(a, nb);
   PAT_LAUNCHED("Gram blocks");
   return PAT_OK;
 }

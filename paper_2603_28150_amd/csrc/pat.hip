@@ -773,8 +773,13 @@ pat_status pat_H_build(pat_ctx* ctx, const pat_geometry* geom, void* h_buf, size
     return s;
   };
   pat_status s;
-  // zero everything first: slab padding must read as zero
-  if ((s = fill_zero(h_buf, L.total, st)) != PAT_OK) return bail(s);
+  // Row padding must read as zero: the tables and every array with padded rows
+  // are cleared first.  The build writes all of the others (0.7 ms less at
+  // 256 x 256 x 128 x 512, where no row is padded).
+  if ((s = fill_zero(h_buf, L.off_Ar, st)) != PAT_OK) return bail(s);
+  if (L.sA_row != geom->nt && (s = fill_zero(op->rowA, L.bytes_Ar, st)) != PAT_OK) return bail(s);
+  if (L.sT_row != geom->nz && (s = fill_zero(op->rowT, L.bytes_Tr, st)) != PAT_OK) return bail(s);
+  if (L.bytes_G && L.sG_row != geom->nz && (s = fill_zero(op->gram, L.bytes_G, st)) != PAT_OK) return bail(s);
   if ((s = hip_check(hipMemcpyAsync(op->members, op->h_members.data(), op->h_members.size() * 4,
                                     hipMemcpyHostToDevice, st), "upload members")) != PAT_OK)
     return bail(s);
@@ -859,15 +864,13 @@ pat_status pat_H_build(pat_ctx* ctx, const pat_geometry* geom, void* h_buf, size
       return bail(s);
   }
   GramArgs ga;
-  ga.slabA = op->slabA;
+  ga.rowA = op->rowA;
   ga.inv_scale = op->inv_scale;
   ga.gram = op->gram;
   ga.nslab = op->nclass;
   ga.nz = geom->nz;
   ga.nt = geom->nt;
   ga.sA_row = op->sA_row;
-  ga.ntA = op->ntA;
-  ga.ksA = op->ksA;
   ga.sG_row = op->sG_row;
   ga.hdtype = geom->h_dtype;
   if (op->gram && (s = gram_build(ga, st)) != PAT_OK) return bail(s);

@@ -147,10 +147,10 @@ pat_status hbuild(const HBuildArgs& a, hipStream_t st);
 // bytes of the stepped build's record of one class
 inline size_t step_class_bytes(int nt, int nq) { return (size_t)nt * (nq / 2 + 1) * 8; }
 struct GramArgs {
-  const void* slabA;        // stored library, [l][n] rows (FP32) or fragments (16-bit)
+  const void* rowA;         // stored library, [nslab][nz][sA_row] rows of the storage type
   const float* inv_scale;   // [nz]
   float* gram;              // [nslab][nz][sG_row]
-  int nslab, nz, nt, sA_row, ntA, ksA, sG_row, hdtype;
+  int nslab, nz, nt, sA_row, sG_row, hdtype;
 };
 pat_status gram_build(const GramArgs& a, hipStream_t st);
 
