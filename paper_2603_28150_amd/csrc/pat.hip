@@ -48,8 +48,8 @@ struct pat_op {
   int32_t* kexpA;     // FP32: [nclass][nt] exponent of each [n][l] row (A's k rows), else null
   int32_t* kexpT;     // FP32: [nclass][nz] exponent of each [l][n] row (A^T's k rows), else null
   int sG_row;
-  pat::FftChirp chirp;  // chirp-z tables of axes that are not fast FFT sizes
-  std::vector<float2> h_cz;  // their host copy: c and the kernel DFT, x then y
+  pat::FftDense dense;  // root tables of axes that are not fast FFT sizes
+  std::vector<float2> h_roots;  // their host copy, x then y
   std::vector<int32_t> h_members, h_kclass, h_cls_freq, h_rowmap, h_item_slab;
   std::vector<int4> h_groups;
   std::vector<double> h_ir;  // sensor response taps folded into the library
@@ -109,47 +109,14 @@ static bool fft_size(int v) {
 }
 
 // other even lengths in [16, 512] (the paper's 202 and 326 among them) run as
-// chirp-z transforms: a circular convolution of length chirp_m(n), the
-// smallest power of two >= 2n - 1
-static bool chirp_size(int v) { return !fft_size(v) && v >= 16 && v <= 512 && v % 2 == 0; }
-static int chirp_m(int n) {
-  int m = 64;
-  while (m < 2 * n - 1) m <<= 1;
-  return m;
-}
+// dense transforms on the matrix cores
+static bool dense_size(int v) { return !fft_size(v) && v >= 16 && v <= 512 && v % 2 == 0; }
 
-// c[k] = exp(i pi k^2 / n), k < n, then the m-point DFT of the even kernel
-// b[j] = c[|j|] (|j| < n, j taken mod m) divided by m; float64, rounded once
-static void chirp_tables(int n, int m, std::vector<float2>& out) {
-  const double pi = 3.141592653589793238462643383279502884;
-  std::vector<double> cr(n), ci(n);
-  for (int k = 0; k < n; ++k) {
-    const long long r = ((long long)k * k) % (2LL * n);  // exact phase reduction
-    cr[k] = std::cos(pi * (double)r / n);
-    ci[k] = std::sin(pi * (double)r / n);
-    out.push_back(make_float2((float)cr[k], (float)ci[k]));
-  }
-  std::vector<double> br(m, 0.0), bi(m, 0.0);
-  for (int j = 0; j < n; ++j) {
-    br[j] = cr[j];
-    bi[j] = ci[j];
-    if (j > 0) {
-      br[m - j] = cr[j];
-      bi[m - j] = ci[j];
-    }
-  }
-  for (int k = 0; k < m; ++k) {
-    double sr = 0.0, si = 0.0;
-    for (int j = 0; j < m; ++j) {
-      if (br[j] == 0.0 && bi[j] == 0.0) continue;
-      const long long e = ((long long)k * j) % m;
-      const double a = -2.0 * pi * (double)e / m;
-      const double ca = std::cos(a), sa = std::sin(a);
-      sr += br[j] * ca - bi[j] * sa;
-      si += br[j] * sa + bi[j] * ca;
-    }
-    out.push_back(make_float2((float)(sr / m), (float)(si / m)));
-  }
+// cos, sin(2 pi k / n), k < n, in float64, rounded once
+static void root_table(int n, std::vector<float2>& out) {
+  const double two_pi = 6.283185307179586476925286766559;
+  for (int k = 0; k < n; ++k)
+    out.push_back(make_float2((float)std::cos(two_pi * k / n), (float)std::sin(two_pi * k / n)));
 }
 
 static int default_nq(const pat_geometry& g) {
@@ -202,13 +169,13 @@ static pat_status check_geometry(const pat_geometry* g) {
   if (g->boundary != PAT_BOUNDARY_PERIODIC && g->boundary != PAT_BOUNDARY_LINEAR)
     return fail(PAT_EINVAL, "unknown boundary");
   if (g->boundary == PAT_BOUNDARY_PERIODIC &&
-      (!(fft_size(g->nx) || chirp_size(g->nx)) || !(fft_size(g->ny) || chirp_size(g->ny))))
+      (!(fft_size(g->nx) || dense_size(g->nx)) || !(fft_size(g->ny) || dense_size(g->ny))))
     return fail(PAT_EUNSUPPORTED, "periodic: nx and ny must be transform sizes (16, 32, 48, 64, 72, 96, 108, 128, "
                                   "144, 192, 216, 256, 288, 384, 432, 512, 576, 768, 864, 1024) or even "
-                                  "lengths in [16, 512] (chirp-z)");
-  if (g->boundary == PAT_BOUNDARY_PERIODIC && (chirp_size(g->nx) || chirp_size(g->ny)) &&
+                                  "lengths in [16, 512]");
+  if (g->boundary == PAT_BOUNDARY_PERIODIC && (dense_size(g->nx) || dense_size(g->ny)) &&
       (g->sx > 1 || g->sy > 1))
-    return fail(PAT_EUNSUPPORTED, "scan-grid sampling needs fast transform sizes (no chirp-z axis)");
+    return fail(PAT_EUNSUPPORTED, "scan-grid sampling needs fast transform sizes along both axes");
   if (g->boundary == PAT_BOUNDARY_LINEAR && (g->nx < 4 || g->nx > 512 || g->ny < 1 || g->ny > 512))
     return fail(PAT_EUNSUPPORTED, "linear: nx must be in [4, 512] and ny in [1, 512]");
   if (g->nz > 2048 || g->nt > 2048) return fail(PAT_EUNSUPPORTED, "nz and nt must be <= 2048");
@@ -314,7 +281,7 @@ static Classes make_classes(const pat_geometry& g) {
 }
 
 struct HLayout {
-  size_t off_cz, bytes_cz;
+  size_t off_roots, bytes_roots;
   size_t off_members, off_items, off_groups, off_kclass, off_rowmap, off_freq, off_inv, off_amax, off_ir, off_A,
       off_T, off_Ar, off_Tr, off_G, off_X, total;
   size_t bytes_A, bytes_T, bytes_Ar, bytes_Tr, bytes_G, bytes_X;
@@ -360,10 +327,10 @@ static HLayout h_layout(const pat_geometry& g, const Classes& C) {
   L.off_inv = o;     o = align_up(o + (size_t)g.nz * 4, 256);
   L.off_amax = o;    o = align_up(o + (size_t)g.nz * 8, 256);
   L.off_ir = o;      o = align_up(o + (size_t)g.n_ir * 8, 256);
-  L.bytes_cz = 0;  // chirp-z tables (periodic axes only: the linear periods are fast sizes)
-  if (chirp_size(g.nx)) L.bytes_cz += (size_t)(g.nx + chirp_m(g.nx)) * 8;
-  if (chirp_size(g.ny)) L.bytes_cz += (size_t)(g.ny + chirp_m(g.ny)) * 8;
-  L.off_cz = o;      o = align_up(o + L.bytes_cz, 256);
+  L.bytes_roots = 0;  // dense axes (periodic only: the linear periods are fast sizes)
+  if (dense_size(g.nx)) L.bytes_roots += (size_t)g.nx * 8;
+  if (dense_size(g.ny)) L.bytes_roots += (size_t)g.ny * 8;
+  L.off_roots = o;   o = align_up(o + L.bytes_roots, 256);
   L.sG_row = (int)align_up((size_t)g.nz, 4);
   // Gram blocks serve the normal-operator gradient, which only the periodic,
   // unsampled operator has (see pat_recon_fista)
@@ -586,21 +553,21 @@ static pat_status run_A(pat_op* op, const float* x, float* y, int B, const float
                         hipStream_t st, bool rows_done = false) {
   const pat_geometry& g = op->g;
   if (rows_done)
-    PAT_TRY(fft2_r2c_cols(w.T, w.Xs, op->fx, op->fy, g.ny, B * g.nz, op->rowmap, op->chirp, st));
+    PAT_TRY(fft2_r2c_cols(w.T, w.Xs, op->fx, op->fy, g.ny, B * g.nz, op->rowmap, op->dense, st));
   else
-    PAT_TRY(fft2_r2c(x, w.T, w.Xs, op->fx, op->fy, g.nx, g.ny, 1, 1, B * g.nz, op->rowmap, op->chirp, st));
+    PAT_TRY(fft2_r2c(x, w.T, w.Xs, op->fx, op->fy, g.nx, g.ny, 1, 1, B * g.nz, op->rowmap, op->dense, st));
   PAT_TRY(run_contract(op, false, w.Xs, w.Ds, B, st));
   return fft2_c2r(w.Ds, w.T, y, op->fx, op->fy, g.nx, g.ny, op->sx, op->sy, B * g.nt, inv_area(op), sub,
-                  op->rowmap, op->chirp, st);
+                  op->rowmap, op->dense, st);
 }
 
 // x = A^T y, B data sets
 static pat_status run_AT(pat_op* op, const float* y, float* x, int B, const Work& w, hipStream_t st) {
   const pat_geometry& g = op->g;
-  PAT_TRY(fft2_r2c(y, w.T, w.Ds, op->fx, op->fy, g.nx, g.ny, op->sx, op->sy, B * g.nt, op->rowmap, op->chirp, st));
+  PAT_TRY(fft2_r2c(y, w.T, w.Ds, op->fx, op->fy, g.nx, g.ny, op->sx, op->sy, B * g.nt, op->rowmap, op->dense, st));
   PAT_TRY(run_contract(op, true, w.Ds, w.Xs, B, st));
   return fft2_c2r(w.Xs, w.T, x, op->fx, op->fy, g.nx, g.ny, 1, 1, B * g.nz, inv_area(op), nullptr,
-                  op->rowmap, op->chirp, st);
+                  op->rowmap, op->dense, st);
 }
 
 // FISTA update with the gradient A^T r of B objects (r: data-shaped), the
@@ -612,14 +579,14 @@ static pat_status run_AT_update(pat_op* op, const float* r, float* x, float* z, 
                                 const FistaBatch& p, int32_t* nonfinite, const Work& w, hipStream_t st,
                                 float2* Tnext = nullptr) {
   const pat_geometry& g = op->g;
-  if (!fft2_c2r_fista_ok(g.nx, op->chirp, B * g.nz, g.nz)) {
+  if (!fft2_c2r_fista_ok(g.nx, op->dense, B * g.nz, g.nz)) {
     PAT_TRY(run_AT(op, r, w.U, B, w, st));
     return fista_update(x, z, w.U, (long long)g.nz * g.nx * g.ny, B, p, nonfinite, st);
   }
-  PAT_TRY(fft2_r2c(r, w.T, w.Ds, op->fx, op->fy, g.nx, g.ny, op->sx, op->sy, B * g.nt, op->rowmap, op->chirp, st));
+  PAT_TRY(fft2_r2c(r, w.T, w.Ds, op->fx, op->fy, g.nx, g.ny, op->sx, op->sy, B * g.nt, op->rowmap, op->dense, st));
   PAT_TRY(run_contract(op, true, w.Ds, w.Xs, B, st));
   return fft2_c2r_fista(w.Xs, w.T, z, x, op->fx, op->fy, g.nx, g.ny, B * g.nz, g.nz, inv_area(op), nullptr,
-                        op->rowmap, op->chirp, p, nonfinite, Tnext, st);
+                        op->rowmap, op->dense, p, nonfinite, Tnext, st);
 }
 
 // FISTA update with the Gram-path gradient: the inverse transform of the
@@ -630,13 +597,13 @@ static pat_status gram_update(pat_op* op, const float2* gs, const float* sub, fl
                               const FistaBatch& p, int32_t* nonfinite, const Work& w, hipStream_t st,
                               float2* Tnext = nullptr) {
   const pat_geometry& g = op->g;
-  if (!fft2_c2r_fista_ok(g.nx, op->chirp, B * g.nz, g.nz)) {
+  if (!fft2_c2r_fista_ok(g.nx, op->dense, B * g.nz, g.nz)) {
     PAT_TRY(fft2_c2r(gs, w.T, w.U, op->fx, op->fy, g.nx, g.ny, 1, 1, B * g.nz, inv_area(op), sub,
-                     op->rowmap, op->chirp, st));
+                     op->rowmap, op->dense, st));
     return fista_update(x, z, w.U, (long long)g.nz * g.nx * g.ny, B, p, nonfinite, st);
   }
   return fft2_c2r_fista(gs, w.T, z, x, op->fx, op->fy, g.nx, g.ny, B * g.nz, g.nz, inv_area(op), sub,
-                        op->rowmap, op->chirp, p, nonfinite, Tnext, st);
+                        op->rowmap, op->dense, p, nonfinite, Tnext, st);
 }
 
 }  // namespace pat
@@ -803,24 +770,18 @@ pat_status pat_H_build(pat_ctx* ctx, const pat_geometry* geom, void* h_buf, size
       (s = hip_check(hipMemcpyAsync(d_ir, op->h_ir.data(), op->h_ir.size() * 8, hipMemcpyHostToDevice, st),
                      "upload sensor response")) != PAT_OK)
     return bail(s);
-  if (L.bytes_cz) {  // chirp-z tables of the transform axes that need them
-    float2* d_cz = reinterpret_cast<float2*>(op->hbuf + L.off_cz);
-    const int nxg = op->fx, nyg = op->fy;
-    if (chirp_size(nxg)) {
-      chirp_tables(nxg, chirp_m(nxg), op->h_cz);
-      op->chirp.cx = d_cz;
-      op->chirp.bx = d_cz + nxg;
-      op->chirp.mx = chirp_m(nxg);
+  if (L.bytes_roots) {  // root tables of the transform axes that need them
+    float2* d_roots = reinterpret_cast<float2*>(op->hbuf + L.off_roots);
+    if (dense_size(op->fx)) {
+      root_table(op->fx, op->h_roots);
+      op->dense.tx = d_roots;
     }
-    if (chirp_size(nyg)) {
-      const size_t o0 = op->h_cz.size();
-      chirp_tables(nyg, chirp_m(nyg), op->h_cz);
-      op->chirp.cy = d_cz + o0;
-      op->chirp.by = d_cz + o0 + nyg;
-      op->chirp.my = chirp_m(nyg);
+    if (dense_size(op->fy)) {
+      op->dense.ty = d_roots + op->h_roots.size();
+      root_table(op->fy, op->h_roots);
     }
-    if ((s = hip_check(hipMemcpyAsync(d_cz, op->h_cz.data(), op->h_cz.size() * sizeof(float2),
-                                      hipMemcpyHostToDevice, st), "upload chirp-z tables")) != PAT_OK)
+    if ((s = hip_check(hipMemcpyAsync(d_roots, op->h_roots.data(), op->h_roots.size() * sizeof(float2),
+                                      hipMemcpyHostToDevice, st), "upload root tables")) != PAT_OK)
       return bail(s);
   }
   HBuildArgs a;
@@ -984,7 +945,7 @@ pat_status pat_spectrum(pat_op* op, const float* f, float* spec, int32_t S, void
   PAT_TRY(check_ptr(f, "f"));
   PAT_TRY(check_ptr(spec, "spec"));
   return fft2_r2c(f, w.T, (float2*)spec, op->fx, op->fy, op->g.nx, op->g.ny, 1, 1, S, op->rowmap,
-                  op->chirp, (hipStream_t)stream);
+                  op->dense, (hipStream_t)stream);
 }
 
 pat_status pat_inverse_spectrum(pat_op* op, const float* spec, float* f, int32_t S, const float* sub,
@@ -995,7 +956,7 @@ pat_status pat_inverse_spectrum(pat_op* op, const float* spec, float* f, int32_t
   PAT_TRY(check_ptr(spec, "spec"));
   if (sub) PAT_TRY(check_ptr(sub, "sub"));
   return fft2_c2r((const float2*)spec, w.T, f, op->fx, op->fy, op->g.nx, op->g.ny, 1, 1, S,
-                  inv_area(op), sub, op->rowmap, op->chirp, (hipStream_t)stream);
+                  inv_area(op), sub, op->rowmap, op->dense, (hipStream_t)stream);
 }
 
 pat_status pat_contract(pat_op* op, int32_t adjoint, const float* in, float* out, int32_t B,
@@ -1025,10 +986,10 @@ pat_status pat_power_norm(pat_op* op, const float* v0, int32_t niter, double* L_
     if (op->gram) {
       // A^T A v per frequency through the Gram blocks: one forward transform,
       // one nz x nz contraction, one inverse transform
-      PAT_TRY(fft2_r2c(w.V, w.T, w.Xs, op->fx, op->fy, g.nx, g.ny, 1, 1, g.nz, op->rowmap, op->chirp, st));
+      PAT_TRY(fft2_r2c(w.V, w.T, w.Xs, op->fx, op->fy, g.nx, g.ny, 1, 1, g.nz, op->rowmap, op->dense, st));
       PAT_TRY(run_gram(op, w.Xs, w.Gs, nullptr, 1, st));
       PAT_TRY(fft2_c2r(w.Gs, w.T, w.U, op->fx, op->fy, g.nx, g.ny, 1, 1, g.nz, inv_area(op), nullptr,
-                       op->rowmap, op->chirp, st));
+                       op->rowmap, op->dense, st));
     } else {
       PAT_TRY(run_A(op, w.V, w.R, 1, nullptr, w, st));
       PAT_TRY(run_AT(op, w.R, w.U, 1, w, st));
@@ -1068,10 +1029,10 @@ pat_status pat_recon_fista(pat_op* op, const float* d, float* x, int32_t niter, 
   const bool normal = op->gram != nullptr;
   if (normal) {
     // b^ = spectrum of A^T d (the adjoint up to its inverse transform), once
-    PAT_TRY(fft2_r2c(d, w.T, w.Ds, op->fx, op->fy, g.nx, g.ny, op->sx, op->sy, g.nt, op->rowmap, op->chirp, st));
+    PAT_TRY(fft2_r2c(d, w.T, w.Ds, op->fx, op->fy, g.nx, g.ny, op->sx, op->sy, g.nt, op->rowmap, op->dense, st));
     PAT_TRY(run_contract(op, true, w.Ds, w.Bs, 1, st));
     if (trace) {
-      PAT_TRY(fft2_c2r(w.Bs, w.T, w.V, op->fx, op->fy, g.nx, g.ny, 1, 1, g.nz, inv, nullptr, op->rowmap, op->chirp, st));  // b = A^T d
+      PAT_TRY(fft2_c2r(w.Bs, w.T, w.V, op->fx, op->fy, g.nx, g.ny, 1, 1, g.nz, inv, nullptr, op->rowmap, op->dense, st));  // b = A^T d
       PAT_TRY(dot_f64(d, d, nd, w.part64, w.s64 + 2, st));
     }
   } else if (trace) {
@@ -1082,7 +1043,7 @@ pat_status pat_recon_fista(pat_op* op, const float* d, float* x, int32_t niter, 
   double t = 1.0;
   FistaBatch p;
   std::memset(&p, 0, sizeof(p));
-  const bool chain = !trace && fft2_c2r_fista_ok(g.nx, op->chirp, g.nz, g.nz);
+  const bool chain = !trace && fft2_c2r_fista_ok(g.nx, op->dense, g.nz, g.nz);
   bool rows_done = false;  // w.T holds the first forward pass on z
   for (int k = 1; k <= niter; ++k) {
     double beta = 0.0;
@@ -1101,14 +1062,14 @@ pat_status pat_recon_fista(pat_op* op, const float* d, float* x, int32_t niter, 
     if (normal) {
       // gradient A^T (A z - d) = A^T A z - A^T d, per frequency: G z^ - b^
       if (rows_done)
-        PAT_TRY(fft2_r2c_cols(w.T, w.Xs, op->fx, op->fy, g.ny, g.nz, op->rowmap, op->chirp, st));
+        PAT_TRY(fft2_r2c_cols(w.T, w.Xs, op->fx, op->fy, g.ny, g.nz, op->rowmap, op->dense, st));
       else
-        PAT_TRY(fft2_r2c(w.Z, w.T, w.Xs, op->fx, op->fy, g.nx, g.ny, 1, 1, g.nz, op->rowmap, op->chirp, st));
+        PAT_TRY(fft2_r2c(w.Z, w.T, w.Xs, op->fx, op->fy, g.nx, g.ny, 1, 1, g.nz, op->rowmap, op->dense, st));
       PAT_TRY(run_gram(op, w.Xs, w.Gs, w.Bs, 1, st));
       if (trace) {
         // the data term needs the gradient itself:
         // 1/2 ||A z - d||^2 = 1/2 (<z, g> - <z, b> + ||d||^2), float64 sums
-        PAT_TRY(fft2_c2r(w.Gs, w.T, w.U, op->fx, op->fy, g.nx, g.ny, 1, 1, g.nz, inv, nullptr, op->rowmap, op->chirp, st));
+        PAT_TRY(fft2_c2r(w.Gs, w.T, w.U, op->fx, op->fy, g.nx, g.ny, 1, 1, g.nz, inv, nullptr, op->rowmap, op->dense, st));
         PAT_TRY(dot_f64(w.Z, w.U, n, w.part64, w.s64 + 0, st));
         PAT_TRY(dot_f64(w.Z, w.V, n, w.part64, w.s64 + 1, st));
         PAT_TRY(trace_combine(trace + (k - 1), w.s64, st));
@@ -1180,7 +1141,7 @@ pat_status pat_fista_step_normal(pat_op* op, int32_t B, const float* atd, float*
     p.o[b].nonneg = nonneg[b] ? 1 : 0;
   }
   const pat_geometry& g = op->g;
-  PAT_TRY(fft2_r2c(z, w.T, w.Xs, op->fx, op->fy, g.nx, g.ny, 1, 1, B * g.nz, op->rowmap, op->chirp, st));
+  PAT_TRY(fft2_r2c(z, w.T, w.Xs, op->fx, op->fy, g.nx, g.ny, 1, 1, B * g.nz, op->rowmap, op->dense, st));
   PAT_TRY(run_gram(op, w.Xs, w.Gs, nullptr, B, st));
   return gram_update(op, w.Gs, atd, x, z, B, p, nonfinite, w, st);  // gradient A^T A z - A^T d
 }

@@ -44,30 +44,31 @@ inline int spec_stride(int S) { return (S + 63) / 64 * 64 + 32; }
 //   row-transformed  T[(j*nh + m) * rs + s]   (y not yet transformed)
 // Forward transforms are unnormalised; the inverse multiplies by `scale`.
 pat_status fft_init_device();  // uploads the twiddle table to the current device
-// Chirp-z tables of an axis whose length n is not a fast FFT size: c[n]
-// (exp(i pi k^2 / n), k < n) and the m-point DFT of the chirp kernel over m
-// (m a power of two >= 2n - 1), device arrays; m = 0: the axis uses the fast
-// transforms.
-struct FftChirp {
-  const float2* cx = nullptr;
-  const float2* bx = nullptr;
-  int mx = 0;
-  const float2* cy = nullptr;
-  const float2* by = nullptr;
-  int my = 0;
+// Axes whose length n is not a fast FFT size: tables cos, sin(2 pi k / n),
+// k < n (device); null: the axis uses the fast transforms.
+struct FftDense {
+  const float2* tx = nullptr;
+  const float2* ty = nullptr;
 };
+// Row and column passes of such axes (fft_dense.hip); in and out as the fast
+// passes' (T row-transformed, X spectrum rows by the maps), whole slices.
+pat_status dense_rows_r2c(const float* f, float2* T, int ny, int N, int S, int rs, const float2* tw, hipStream_t st);
+pat_status dense_rows_c2r(const float2* T, float* f, int ny, int N, int S, int rs, float scale, const float* sub,
+                          const float2* tw, hipStream_t st);
+pat_status dense_cols(int dir, const float2* in, float2* out, int nh, int N, int S, int rs, const int32_t* imap,
+                      const int32_t* omap, const float2* tw, hipStream_t st);
 // f holds S slices covering the nxw x nyw window of the fx x fy transform
-// grid (fast sizes, or chirp-z lengths), sampled every sx columns and sy rows:
+// grid (fast sizes, or dense lengths), sampled every sx columns and sy rows:
 // f[s][nyw/sy][nxw/sx].  Zero-padding and zero-filling on the way in,
 // cropping and sampling on the way out.
-// An axis with chirp-z tables (ch.mx / ch.my > 0) must be covered whole and
+// An axis with a dense table must be covered whole and
 // unsampled.
 pat_status fft2_r2c(const float* f, float2* T, float2* X, int fx, int fy, int nxw, int nyw, int sx,
-                    int sy, int S, const int32_t* rowmap, const FftChirp& ch, hipStream_t st);
+                    int sy, int S, const int32_t* rowmap, const FftDense& dn, hipStream_t st);
 // f = scale * c2r(X) - sub (sub may be null; same layout as f)
 pat_status fft2_c2r(const float2* X, float2* T, float* f, int fx, int fy, int nxw, int nyw, int sx,
                     int sy, int S, float scale, const float* sub, const int32_t* rowmap,
-                    const FftChirp& ch, hipStream_t st);
+                    const FftDense& dn, hipStream_t st);
 
 // ------------------------------------------------------ contraction (float32 matrix instructions)
 // out[r][obj*nj + j] = sum_i slab_s[i][j] * in[r][obj*ni + i] (* scales) for
@@ -188,15 +189,15 @@ pat_status fista_update(float* x, float* z, const float* g, long long n_per_obj,
 // beforehand).  Tnext != null: also the next iteration's forward row pass on
 // the new z (unsampled slices, as fft2_r2c's first pass writes it), in the
 // layout of T; Tnext may be T.
-bool fft2_c2r_fista_ok(int nxw, const FftChirp& ch, int S, int per_obj);
+bool fft2_c2r_fista_ok(int nxw, const FftDense& dn, int S, int per_obj);
 pat_status fft2_c2r_fista(const float2* X, float2* T, float* z, float* x, int fx, int fy, int nxw,
                           int nyw, int S, int per_obj, float scale, const float* sub,
-                          const int32_t* rowmap, const FftChirp& ch, const FistaBatch& p,
+                          const int32_t* rowmap, const FftDense& dn, const FistaBatch& p,
                           int32_t* nonfinite, float2* Tnext, hipStream_t st);
 // the second (column) pass of fft2_r2c alone, for unsampled slices whose
 // first pass is already in T (from fft2_c2r_fista with Tnext)
 pat_status fft2_r2c_cols(const float2* T, float2* X, int fx, int fy, int nyw, int S, const int32_t* rowmap,
-                         const FftChirp& ch, hipStream_t st);
+                         const FftDense& dn, hipStream_t st);
 
 constexpr int kRedBlocks = 512;
 
