@@ -354,10 +354,9 @@ static HLayout h_layout(const pat_geometry& g, const Classes& C) {
 struct Work {
   float2 *Xs, *Ds, *T, *Bs, *Gs;
   float *V, *U, *Z, *R;
-  double* part64;
-  float* part32;
+  double* part64;  // kRedBlocks partial sums
   double* s64;   // 8 doubles
-  float* s32;    // 8 floats + trace of the power iteration
+  float* L;      // trace of the power iteration
   size_t total;
 };
 constexpr int kMaxPowerIter = 4096;
@@ -392,9 +391,8 @@ static Work work_layout(const pat_op* op, int B, char* base, bool apply_only = f
   w.Z = (float*)take(Sz * nxy * 4);
   w.R = (float*)take(St * nxy * 4);
   w.part64 = (double*)take(kRedBlocks * 8);
-  w.part32 = (float*)take(kRedBlocks * 4);
   w.s64 = (double*)take(8 * 8);
-  w.s32 = (float*)take((8 + kMaxPowerIter) * 4);
+  w.L = (float*)take(kMaxPowerIter * 4);
   w.total = o;
   return w;
 }
@@ -979,9 +977,8 @@ pat_status pat_power_norm(pat_op* op, const float* v0, int32_t niter, double* L_
   hipStream_t st = (hipStream_t)stream;
   const pat_geometry& g = op->g;
   const long long n = (long long)g.nz * g.nx * g.ny;
-  float* Ls = w.s32 + 8;
-  PAT_TRY(dot_f32(v0, v0, n, w.part32, w.s32, 1.f, st));
-  PAT_TRY(scale_rsqrt(w.V, v0, n, w.s32, st));
+  float2* part = reinterpret_cast<float2*>(w.part64);  // kRedBlocks pairs of float
+  PAT_TRY(power_normalise(w.V, v0, v0, n, part, nullptr, st));
   for (int i = 0; i < niter; ++i) {
     if (op->gram) {
       // A^T A v per frequency through the Gram blocks: one forward transform,
@@ -994,12 +991,10 @@ pat_status pat_power_norm(pat_op* op, const float* v0, int32_t niter, double* L_
       PAT_TRY(run_A(op, w.V, w.R, 1, nullptr, w, st));
       PAT_TRY(run_AT(op, w.R, w.U, 1, w, st));
     }
-    PAT_TRY(dot_f32(w.V, w.U, n, w.part32, Ls + i, 1.f, st));
-    PAT_TRY(dot_f32(w.U, w.U, n, w.part32, w.s32 + 1, 1.f, st));
-    PAT_TRY(scale_rsqrt(w.V, w.U, n, w.s32 + 1, st));
+    PAT_TRY(power_normalise(w.V, w.V, w.U, n, part, w.L + i, st));
   }
   std::vector<float> hL(niter);
-  PAT_HIP(hipMemcpyAsync(hL.data(), Ls, niter * sizeof(float), hipMemcpyDeviceToHost, st));
+  PAT_HIP(hipMemcpyAsync(hL.data(), w.L, niter * sizeof(float), hipMemcpyDeviceToHost, st));
   PAT_HIP(hipStreamSynchronize(st));
   *L_out = hL[niter - 1];
   if (L_trace)

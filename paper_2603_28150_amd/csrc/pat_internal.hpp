@@ -161,15 +161,15 @@ pat_status hexport(const void* slabA, int hdtype, const int32_t* kclass, const f
 
 // ------------------------------------------------------- vector kernels
 pat_status fill_zero(void* p, size_t bytes, hipStream_t st);
-// partial sums of a*b (or a*a when b == a) over n floats into part[nblk]; float or double accumulation
-pat_status dot_f32(const float* a, const float* b, long long n, float* part, float* result,
-                   float post_scale, hipStream_t st);
+// <a, b> over n floats, accumulated in double through part[kRedBlocks]
 pat_status dot_f64(const float* a, const float* b, long long n, double* part, double* result,
                    hipStream_t st);
 // out[0] = (s[0] - s[1] + s[2]) / 2
 pat_status trace_combine(float* out, const double* s, hipStream_t st);
-// dst = src / sqrt(*nrm2)
-pat_status scale_rsqrt(float* dst, const float* src, long long n, const float* nrm2, hipStream_t st);
+// dst = u / sqrt(<u, u>) and, if vu, *vu = <v, u>, in float32 through
+// part[kRedBlocks]; pointers to 16 bytes, dst may be v but not u
+pat_status power_normalise(float* dst, const float* v, const float* u, long long n, float2* part,
+                           float* vu, hipStream_t st);
 
 struct FistaObj {
   float tau, thr, beta;
