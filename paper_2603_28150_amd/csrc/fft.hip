@@ -13,7 +13,8 @@
 //   columns: complex transforms along y on the frequency-major layout, slices
 //            fastest, so that loads and stores are contiguous across threads.
 // Twiddles exp(-2 pi i e / N) of every size N are tabulated on the host in
-// float64 and rounded once to float32.
+// float64 and rounded once to float32.  Small grids take both passes in one
+// kernel (fft_small.hpp).
 //
 // Transform sizes and data extents are separate: slices cover an nx_d x ny_d
 // window of the fx x fy transform grid (nx_d <= fx, ny_d <= fy), sampled at
@@ -22,6 +23,7 @@
 // never read (forward) and never written (inverse), so the zero-padded
 // linear convolution and the scan-grid sampling cost no extra HBM traffic.
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "dft.hpp"
@@ -66,6 +68,12 @@ pat_status fft_init_device() {
                             hipMemcpyHostToDevice));
   return PAT_OK;
 }
+
+}  // namespace pat
+
+#include "fft_small.hpp"
+
+namespace pat {
 
 // exp(DIR 2 pi i e / N), e < N, into LDS
 template <int N, int DIR>
@@ -627,6 +635,38 @@ static bool extents_ok(int fx, int fy, int nxw, int nyw, int sx, int sy) {
   return nxw / sx >= 1 && nyw / sy >= 1;
 }
 
+// Grids and slice counts that one kernel transforms (k_fft_small_*): both axes
+// of 16 to 64 points (the grid fits a workgroup's LDS several times per CU),
+// every sample, at most 4 M values.  Up to there two passes are bound by their
+// launches and their latency, beyond it by bytes, and then whole lines along
+// the slices are the better access.  One forward and one inverse transform,
+// two passes and one: 32 x 32, 512 slices 23.0 and 17.4 us, 4,096 slices (4 M)
+// 37.7 and 32.0; 64 x 64, 512 slices 29.3 and 20.1, 1,024 (4 M) 36.0 and 35.0,
+// 2,048 53.1 and 63.7; 48 x 48, 1,024 slices 30.4 and 21.9, 2,048 (4.7 M) 37.8
+// and 46.2.
+static bool small_grid(int fx, int fy, int sx, int sy, int S) {
+  auto ok = [](int n) { return n == 16 || n == 32 || n == 48 || n == 64; };
+  return ok(fx) && ok(fy) && sx == 1 && sy == 1 && (long long)S * fx * fy <= (1LL << 22);
+}
+
+template <typename F>
+static void small_dispatch(int fx, int fy, F&& go) {
+  auto along_y = [&](auto nx) {
+    constexpr int NX = decltype(nx)::value;
+    if (fy == 16) go(std::integral_constant<int, NX>(), std::integral_constant<int, 16>());
+    if (fy == 32) go(std::integral_constant<int, NX>(), std::integral_constant<int, 32>());
+    if (fy == 48) go(std::integral_constant<int, NX>(), std::integral_constant<int, 48>());
+    if (fy == 64) go(std::integral_constant<int, NX>(), std::integral_constant<int, 64>());
+  };
+  if (fx == 16) along_y(std::integral_constant<int, 16>());
+  if (fx == 32) along_y(std::integral_constant<int, 32>());
+  if (fx == 48) along_y(std::integral_constant<int, 48>());
+  if (fx == 64) along_y(std::integral_constant<int, 64>());
+}
+
+// workgroups of a pair of slices each, in whole groups of 64 (small_pair)
+static int small_blocks(int S) { return ((S + 1) / 2 + 63) / 64 * 64; }
+
 pat_status fft2_r2c(const float* f, float2* T, float2* X, int fx, int fy, int nxw, int nyw, int sx,
                     int sy, int S, const int32_t* rowmap, const FftDense& dn, hipStream_t st) {
   if (S <= 0) return PAT_OK;
@@ -637,6 +677,14 @@ pat_status fft2_r2c(const float* f, float2* T, float2* X, int fx, int fy, int nx
   const int nxc = nxw / sx, nyc = nyw / sy;
   if ((dn.tx && (nxw != fx || sx != 1)) || (dn.ty && (nyw != fy || sy != 1)))
     return fail(PAT_EUNSUPPORTED, "fft: axes without a fast transform take whole, unsampled slices");
+  if (small_grid(fx, fy, sx, sy, S)) {
+    small_dispatch(fx, fy, [&](auto nx, auto ny) {
+      constexpr int NX = decltype(nx)::value, NY = decltype(ny)::value;
+      k_fft_small_r2c<NX, NY><<<small_blocks(S), SmallGrid<NX, NY>::NT, 0, st>>>(f, X, nyc, nxc, S, rs, rowmap);
+    });
+    PAT_LAUNCHED("fft r2c");
+    return PAT_OK;
+  }
   auto columns = [&]() {
     if (dn.ty) return dense_cols(-1, T, X, nh, fy, S, rs, nullptr, rowmap, dn.ty, st);
     return cols<-1>(T, X, fy, nh, S, rs, nullptr, rowmap, nyc, sy, fy, 1, st);
@@ -667,6 +715,15 @@ pat_status fft2_c2r(const float2* X, float2* T, float* f, int fx, int fy, int nx
   const int nxc = nxw / sx, nyc = nyw / sy;
   if ((dn.tx && (nxw != fx || sx != 1)) || (dn.ty && (nyw != fy || sy != 1)))
     return fail(PAT_EUNSUPPORTED, "fft: axes without a fast transform take whole, unsampled slices");
+  if (small_grid(fx, fy, sx, sy, S)) {
+    small_dispatch(fx, fy, [&](auto nx, auto ny) {
+      constexpr int NX = decltype(nx)::value, NY = decltype(ny)::value;
+      k_fft_small_c2r<NX, NY><<<small_blocks(S), SmallGrid<NX, NY>::NT, 0, st>>>(X, f, nyc, nxc, S, rs, scale, sub,
+                                                                               rowmap);
+    });
+    PAT_LAUNCHED("fft c2r");
+    return PAT_OK;
+  }
   if (dn.ty)
     PAT_TRY(dense_cols(+1, X, T, nh, fy, S, rs, rowmap, nullptr, dn.ty, st));
   else
