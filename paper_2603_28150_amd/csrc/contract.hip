@@ -497,6 +497,13 @@ pat_status contract(const ContractArgs& a, int hdtype, hipStream_t st) {
     return fail(PAT_EUNSUPPORTED, "contraction slab or spectrum rows beyond 32-bit offsets");
   // one object on the two-member fold: the vector units' kernel
   if (a.members <= 2 && a.B == 1 && !a.out_sub && !a.gram) return contract_pair(a, hdtype, st);
+  // one object's Gram products from half of each block, where rows start at
+  // whole 64-byte pieces and the groups, a wave each, fill the CUs (a step at
+  // 108 x 108 x 100, 400-byte rows: 42.0 us whole, 44.5 half; 64 x 64 x 96, 561
+  // groups: 25.4 and 27.2; 96 x 96 x 128, 1,225 groups: 39.7 and 38.4); up to 64
+  // rows always (64 x 64 x 64: 24.4 and 24.5; 128 x 128 x 52: 35.5 and 34.2)
+  if (a.gram && a.B == 1 && (a.ni <= 64 || (a.ni <= 128 && a.s_row % 16 == 0 && a.ngroup >= 1024)))
+    return contract_sym(a, a.reuse_bytes > kCacheBytes, st);
   if (hdtype == PAT_H_BF16) return launch_t<bf16_t, 1>(a, st);
   if (hdtype == PAT_H_F16) return launch_t<f16_t, 1>(a, st);
   const int pairs = a.members * a.B;
