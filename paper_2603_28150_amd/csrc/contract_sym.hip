@@ -1,4 +1,4 @@
-// Gram products of one object from half of every block (G is symmetric).
+// Gram products from half of every block (G is symmetric).
 //
 // FISTA and the power iteration multiply each class's nz x nz Gram block with
 // the spectra of its member frequencies once per step; for one object reading
@@ -20,7 +20,9 @@
 //
 // A step of FISTA, whole blocks and this: 256 x 256 x 128, 158 us, now 142;
 // 256 x 256 x 30, 62 and 46; 128 x 128 x 96, 43.2 and 40.8; 256 x 192 x 96 (two
-// members), 143 and 118.
+// members), 143 and 118.  Of 4 objects: 256 x 256 x 32, 157 and 106; 128 x 128 x
+// 96, 96.8 and 88.5 (there the general kernel reads a value once for all
+// pairs: 4 times fewer loads, but one wave per tile and half the workgroups).
 //
 // Each tile's four instructions form a sum of 16 products of their own, added
 // to y once: no longer a chain of roundings than the general kernel's.
@@ -36,19 +38,25 @@ __device__ __forceinline__ void wave_order() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
+typedef float v4f8 __attribute__((ext_vector_type(4), aligned(8)));  // two complex values, 8-byte aligned
+
 constexpr int kUnits = 4;  // units in flight
 
 // T tiles of 16 rows; NT: non-temporal loads; WT: lines written through
 template <int T, bool NT, bool WT>
-__global__ __launch_bounds__(256, 3) void k_contract_sym(ContractArgs a, int per_xcd) {
+__global__ __launch_bounds__(256, 3) void k_contract_sym(ContractArgs a, int per_xcd, int pgroups) {
   constexpr int T2 = (T + 1) / 2;  // units of 16 rows x 32 columns (whole lines) from the diagonal on
   constexpr int N = T2 * (T2 + 1) - T % 2;
   constexpr int D = kUnits < N ? kUnits : N;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // groups in order, one contiguous range per XCD (workgroups go round-robin)
-  const int in_range = (blockIdx.x >> 3) * 4 + w, t = (blockIdx.x & 7) * per_xcd + in_range;
-  if (in_range >= per_xcd || t >= a.ngroup) return;
+  // units (group, 8 pairs) in order, one contiguous range per XCD (workgroups
+  // go round-robin): the units of a group read its block at about the same time
+  const int in_range = (blockIdx.x >> 3) * 4 + w, u = (blockIdx.x & 7) * per_xcd + in_range;
+  if (in_range >= per_xcd || u >= a.ngroup * pgroups) return;
+  const int t = u / pgroups, pg0 = 8 * (u - t * pgroups);
   const int4 grp = a.groups[t];  // first spectrum row, members, slab
+  const int np = grp.y * a.B;    // pairs: members times objects
+  if (pg0 >= np) return;
   const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
   const int nz = a.ni, sr = a.s_row;
   constexpr int last = 16 * (T - 1);
@@ -84,9 +92,10 @@ __global__ __launch_bounds__(256, 3) void k_contract_sym(ContractArgs a, int per
   float* wr = turn[w] + lr * 36 + lc;
   const float* rd = turn[w] + c * 36 + 4 * q;
   const float* rt = turn[w] + 4 * q * 36 + c;
-  // x: lane holds rows 4 q + e of tile J for column c (member c / 2, part c % 2)
-  const int mem = min(c >> 1, grp.y - 1);
-  const float* xrow = reinterpret_cast<const float*>(a.in + (size_t)(grp.x + mem) * a.in_rs + 4 * q) + (c & 1);
+  // x: lane holds rows 4 q + e of tile J for column c (pair pg0 + c / 2, part c % 2)
+  const int pr = min(pg0 + (c >> 1), np - 1), mem = a.B == 1 ? pr : pr / a.B, ob = pr - mem * a.B;
+  const float* xrow =
+      reinterpret_cast<const float*>(a.in + (size_t)(grp.x + mem) * a.in_rs + (size_t)ob * nz + 4 * q) + (c & 1);
   v4f x[T], y[T];
 #pragma unroll
   for (int J = 0; J < T; ++J) {
@@ -154,14 +163,14 @@ __global__ __launch_bounds__(256, 3) void k_contract_sym(ContractArgs a, int per
   // rows 16 I + 4 q + r of column c: the lanes of a member's real and imaginary
   // parts exchange two values, then each stores two complex values; four lane
   // groups complete the 128 bytes of a tile in the member's row
-  const size_t o0 = (size_t)(grp.x + (c >> 1)) * a.out_rs + 4 * q + 2 * (c & 1);
-  const bool live = (c >> 1) < grp.y;
+  const size_t o0 = (size_t)(grp.x + mem) * a.out_rs + (size_t)ob * nz + 4 * q + 2 * (c & 1);
+  const bool live = pg0 + (c >> 1) < np;
   v4f sub[T];
 #pragma unroll
   for (int I = 0; I < T; ++I) {
     const int left = live ? nz - (16 * I + 4 * q + 2 * (c & 1)) : 0;
     sub[I] = v4f(0.f);
-    if (a.out_sub && left >= 2) sub[I] = *reinterpret_cast<const v4f*>(a.out_sub + o0 + 16 * I);
+    if (a.out_sub && left >= 2) sub[I] = *reinterpret_cast<const v4f8*>(a.out_sub + o0 + 16 * I);
     if (a.out_sub && left == 1) {
       const float2 s1 = a.out_sub[o0 + 16 * I];
       sub[I][0] = s1.x;
@@ -183,7 +192,7 @@ __global__ __launch_bounds__(256, 3) void k_contract_sym(ContractArgs a, int per
             bits, orow, (int)((unsigned)(o0 + 16 * I - (size_t)grp.x * a.out_rs) * 8u), 0, 16);  // sc1
       }
     } else if (left >= 2) {
-      *reinterpret_cast<v4f*>(a.out + o0 + 16 * I) = v;
+      *reinterpret_cast<v4f8*>(a.out + o0 + 16 * I) = v;
     } else if (left == 1) {
       a.out[o0 + 16 * I] = make_float2(v[0], v[1]);
     }
@@ -192,10 +201,11 @@ __global__ __launch_bounds__(256, 3) void k_contract_sym(ContractArgs a, int per
 
 template <int T>
 static void launch_sym(const ContractArgs& a, bool nt, hipStream_t st) {
-  const int per_xcd = (a.ngroup + 7) / 8;
+  const int pgroups = (a.members * a.B + 7) / 8;
+  const int per_xcd = (a.ngroup * pgroups + 7) / 8;
   const int grid = 8 * ((per_xcd + 3) / 4);
   const bool wt = a.nj % 16 == 0;
-  auto go = [&](auto kernel) { kernel<<<grid, 256, 0, st>>>(a, per_xcd); };
+  auto go = [&](auto kernel) { kernel<<<grid, 256, 0, st>>>(a, per_xcd, pgroups); };
   if (nt && wt) return go(k_contract_sym<T, true, true>);
   if (nt) return go(k_contract_sym<T, true, false>);
   if (wt) return go(k_contract_sym<T, false, true>);

@@ -94,8 +94,7 @@ struct ContractArgs {
 pat_status contract(const ContractArgs& a, int hdtype, hipStream_t st);
 // the same for B = 1 and groups of at most two members (contract sends them here)
 pat_status contract_pair(const ContractArgs& a, int hdtype, hipStream_t st);
-// the same for B = 1 and symmetric float32 slabs of at most 128 rows, reading
-// half of each (nt: non-temporal loads)
+// the same for symmetric float32 slabs of at most 128 rows, reading half of each (nt: non-temporal loads)
 pat_status contract_sym(const ContractArgs& a, bool nt, hipStream_t st);
 
 // ------------------------------------------------------ contraction (MFMA)

@@ -58,3 +58,22 @@ def test_half_blocks(nx, ny, nz):
         zk, xk, t = xn + (t - 1.0) / tn * (xn - xk), xn, tn
     got = op.recon_fista(d, 3, tau, 0.0, nonneg=True).double()
     assert float((got - xk).norm()) <= 1e-5 * float(xk.norm())
+
+
+@pytest.mark.parametrize("nx,ny,nz,B", [(16, 16, 1, 2), (16, 16, 15, 3), (16, 16, 33, 5), (16, 16, 64, 32), (16, 32, 33, 3),
+                                        (16, 32, 64, 4), (16, 32, 47, 9), (96, 96, 77, 2), (96, 96, 80, 3), (64, 64, 80, 2),
+                                        (64, 64, 127, 3), (64, 96, 128, 5)])
+def test_half_blocks_of_several_objects(nx, ny, nz, B):
+    # objects that start at odd multiples of 8 bytes in a spectrum row, pairs
+    # that fill a wave's columns in part, more units than groups
+    op = Operator(Geometry(nx, ny, nz, 12, 1e-4, 1e-4 if nx == ny else 1.1e-4, 1e-4, 2e-7, 1500.0))
+    ata, _ = exact(op)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(nx * 10000 + ny * 100 + nz + B)
+    z = torch.randn((B,) + op.x_shape, generator=gen, device="cuda")
+    x, zero, z0 = torch.zeros_like(z), torch.zeros_like(z), z.clone()
+    op.fista_step_normal(zero, x, z, [0.0] * B, [1.0] * B, [0.0] * B, [False] * B)
+    for b in range(B):
+        ref = ata(z0[b])
+        tol = 1e-5 * max(float(ref.norm()), float(z0[b].norm()))
+        assert float(((z0 - x)[b].double() - ref).norm()) <= tol, b
