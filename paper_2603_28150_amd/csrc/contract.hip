@@ -26,8 +26,8 @@
 // 202 x 202 x 37 x 256 on 432 x 432, 171 / 221, now 144 / 157; 256 x 256 x
 // 128 x 512, 307 / 287, now 300 / 277 (5.9 TB/s); with bf16 slabs 195 / 200,
 // now 179 / 164 (groups of 8 members read a slab once that two items of 4
-// read twice).  FISTA's Gram products (of more than 128 rows, or rows that do
-// not start at whole 64 bytes; contract_sym.hip takes the others) of 4 objects
+// read twice).  FISTA's Gram products (of more than 128 rows, or of one object
+// with rows not of whole 64 bytes; contract_sym.hip takes the others) of 4 objects
 // (two to four pairs of columns per value loaded), per step: 256 x 256 x 128,
 // 590 us, 484 with this; 128 x 128 x 96, 121 and 95.
 #include <algorithm>
@@ -498,14 +498,15 @@ pat_status contract(const ContractArgs& a, int hdtype, hipStream_t st) {
     return fail(PAT_EUNSUPPORTED, "contraction slab or spectrum rows beyond 32-bit offsets");
   // one object on the two-member fold: the vector units' kernel
   if (a.members <= 2 && a.B == 1 && !a.out_sub && !a.gram) return contract_pair(a, hdtype, st);
-  // Gram products from half of each block, where rows start at whole 64-byte
-  // pieces and the units (a group's 8 pairs, a wave each) fill the CUs (a step
-  // of one object at 108 x 108 x 100, 400-byte rows: 42.0 us whole, 44.5 half;
-  // 64 x 64 x 96, 561 units: 25.4 and 27.2; 96 x 96 x 128, 1,225 units: 39.7 and
-  // 38.4); up to 64 rows always (one object at 64 x 64 x 64: 24.4 and 24.5;
+  // Gram products from half of each block, where the units (a group's 8 pairs,
+  // a wave each) fill the CUs and, for one object, rows start at whole 64-byte
+  // pieces (a step of one object at 108 x 108 x 100, 400-byte rows: 42.0 us
+  // whole, 44.5 half; of 2 and 16 at 144 x 144 x 105: 92.9 and 85.8, 600 and 563;
+  // one at 64 x 64 x 96, 561 units: 25.4 and 27.2; at 96 x 96 x 128, 1,225 units:
+  // 39.7 and 38.4); up to 64 rows always (one object at 64 x 64 x 64: 24.4 and 24.5;
   // 128 x 128 x 52: 35.5 and 34.2; 16 objects at 96 x 96 x 13: 92.8 and 44.0)
   const long long units = (long long)a.ngroup * ((a.members * a.B + 7) / 8);
-  if (a.gram && (a.ni <= 64 || (a.ni <= 128 && a.s_row % 16 == 0 && units >= 1024)))
+  if (a.gram && (a.ni <= 64 || (a.ni <= 128 && (a.B > 1 || a.s_row % 16 == 0) && units >= 1024)))
     return contract_sym(a, a.reuse_bytes > kCacheBytes, st);
   if (hdtype == PAT_H_BF16) return launch_t<bf16_t, 1>(a, st);
   if (hdtype == PAT_H_F16) return launch_t<f16_t, 1>(a, st);

@@ -1,7 +1,7 @@
 """Gram products of one object from half of each symmetric block, at the edges
 of its tiles (16 rows) and loads (32 columns), with 8 and with 2 members per
-group, and where the rule for more than 64 rows lets them in (rows of whole 64
-bytes, at least 1,024 groups).
+group, and where the rule for more than 64 rows lets them in (for one object rows
+of whole 64 bytes; at least 1,024 units of 8 pairs).
 
 Against float64 products with the exported library, to the bars of the other
 Gram tests: 1e-5 of the product, or of z where z - A^T A z cancels."""
@@ -62,7 +62,8 @@ def test_half_blocks(nx, ny, nz):
 
 @pytest.mark.parametrize("nx,ny,nz,B", [(16, 16, 1, 2), (16, 16, 15, 3), (16, 16, 33, 5), (16, 16, 64, 32), (16, 32, 33, 3),
                                         (16, 32, 64, 4), (16, 32, 47, 9), (96, 96, 77, 2), (96, 96, 80, 3), (64, 64, 80, 2),
-                                        (64, 64, 127, 3), (64, 96, 128, 5)])
+                                        (64, 64, 127, 3), (64, 96, 128, 5),
+                                        (96, 96, 65, 2), (96, 96, 105, 3), (64, 96, 114, 2)])
 def test_half_blocks_of_several_objects(nx, ny, nz, B):
     # objects that start at odd multiples of 8 bytes in a spectrum row, pairs
     # that fill a wave's columns in part, more units than groups
