@@ -416,6 +416,7 @@ constexpr long long kCacheBytes = 256LL << 20;
 // spectrum bytes: staged, 202 x 202 x 37 x 256 (linear) took 640 instead of
 // 612 us.
 constexpr int kXlRows = 192;
+constexpr size_t kMaxLds = 160 * 1024;  // of a CU
 
 template <typename HT, int CT, int U, bool NT, bool WT, bool XL>
 __global__ __launch_bounds__(256, (CT > 1 ? 2 : 3)) void k_contract(ContractArgs a, int TW, int KP, int tgroups,
@@ -443,7 +444,7 @@ __global__ __launch_bounds__(256, (CT > 1 ? 2 : 3)) void k_contract(ContractArgs
 }
 
 template <typename HT, int CT, int U>
-static void launch_u(const ContractArgs& a, dim3 grid, int TW, int KP, int tgroups, int pgroups, int ntile, bool nt,
+static pat_status launch_u(const ContractArgs& a, dim3 grid, int TW, int KP, int tgroups, int pgroups, int ntile, bool nt,
                      bool xl, hipStream_t st) {
   constexpr int VEC = Slab<HT>::VEC;
   // Written-through lines (whole 128-byte lines only: parts of lines made the
@@ -454,17 +455,24 @@ static void launch_u(const ContractArgs& a, dim3 grid, int TW, int KP, int tgrou
   // 256 x 256 x 128.  A's spectra stay cached for the transform that follows.
   const bool wt = a.nj % 16 == 0 && (a.gram || a.ni >= 256);
   const dim3 block(64 * TW * KP);
+  // the sums that waves of a workgroup pass on and, in the kernels that stage
+  // them, the spectra.  CT = 1 alone stages: the spectra of 32 pairs would
+  // leave room for one workgroup per CU from 289 rows on (a step of 4 and 16
+  // objects at 64 x 64 x 512: 222 and 986 us with that much LDS, 216 and 881
+  // without) and for none beyond 608
   const size_t lds = std::max((size_t)TW * KP * (KP > 1 ? CT : 1) * VEC * 256 * sizeof(float),
-                              xl ? (size_t)8 * CT * xl_stride(a.ni) : 0);
-  auto go = [&](auto kernel) { kernel<<<grid, block, lds, st>>>(a, TW, KP, tgroups, pgroups, ntile); };
+                              xl ? (size_t)8 * xl_stride(a.ni) : 0);
+  if (lds > kMaxLds) return fail(PAT_EUNSUPPORTED, "contraction: sums and spectra do not fit in LDS");
+  auto kernel = nt && wt ? k_contract<HT, CT, U, true, true, false>
+                : nt     ? k_contract<HT, CT, U, true, false, false>
+                : wt     ? k_contract<HT, CT, U, false, true, false>
+                         : k_contract<HT, CT, U, false, false, false>;
   if constexpr (CT == 1) {
-    if (xl && wt) return go(k_contract<HT, CT, U, true, true, true>);
-    if (xl) return go(k_contract<HT, CT, U, true, false, true>);
+    if (xl) kernel = wt ? k_contract<HT, CT, U, true, true, true> : k_contract<HT, CT, U, true, false, true>;
   }
-  if (nt && wt) return go(k_contract<HT, CT, U, true, true, false>);
-  if (nt) return go(k_contract<HT, CT, U, true, false, false>);
-  if (wt) return go(k_contract<HT, CT, U, false, true, false>);
-  go(k_contract<HT, CT, U, false, false, false>);
+  kernel<<<grid, block, lds, st>>>(a, TW, KP, tgroups, pgroups, ntile);
+  PAT_LAUNCHED("contraction");
+  return PAT_OK;
 }
 
 template <typename HT, int CT>
@@ -481,14 +489,11 @@ static pat_status launch_t(const ContractArgs& a, hipStream_t st) {
   if (nblk > 0x7fffffffLL) return fail(PAT_EUNSUPPORTED, "contraction grid too large");
   const dim3 grid((unsigned)nblk);
   const bool nt = a.reuse_bytes > kCacheBytes;
-  const bool xl = nt && a.members > 2 && a.ni >= kXlRows && a.nj >= 64 && (size_t)8 * xl_stride(a.ni) <= 64 * 1024;
+  const bool xl = CT == 1 && nt && a.members > 2 && a.ni >= kXlRows && a.nj >= 64 && (size_t)8 * xl_stride(a.ni) <= 64 * 1024;
   const int share = (a.ni >> 3) / KP;  // row blocks of a wave
   if (CT == 1 && VEC == 4 && share % 4 == 0)
-    launch_u<HT, CT, (CT == 1 && VEC == 4 ? 4 : 2)>(a, grid, TW, KP, tgroups, pgroups, ntile, nt, xl, st);
-  else
-    launch_u<HT, CT, (CT == 4 ? 1 : 2)>(a, grid, TW, KP, tgroups, pgroups, ntile, nt, xl, st);
-  PAT_LAUNCHED("contraction");
-  return PAT_OK;
+    return launch_u<HT, CT, (CT == 1 && VEC == 4 ? 4 : 2)>(a, grid, TW, KP, tgroups, pgroups, ntile, nt, xl, st);
+  return launch_u<HT, CT, (CT == 4 ? 1 : 2)>(a, grid, TW, KP, tgroups, pgroups, ntile, nt, xl, st);
 }
 
 pat_status contract(const ContractArgs& a, int hdtype, hipStream_t st) {

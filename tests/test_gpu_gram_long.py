@@ -1,0 +1,39 @@
+"""Batched Gram products of many rows whose blocks together exceed the 256 MB
+memory-side cache: one, two and three or more objects take different kernels,
+whose needs of LDS must stay within a CU at every depth.
+
+Against float64 products with the exported library, to the bar of the other
+Gram tests: 1e-5 of the product, or of z where z - A^T A z cancels."""
+import pytest
+import torch
+
+from paper_2603_28150_amd.op import Geometry, Operator
+
+pytestmark = pytest.mark.gpu
+
+
+def normal64(op, z):
+    """A^T A z in float64 of [nz, ny, nx] z."""
+    g = op.geom
+    H = op.export_H().double()                                       # [nk, nz, nt]
+    u = torch.fft.rfft2(z.double()).reshape(g.nz, -1).t()
+    u = torch.view_as_real(u.contiguous())                           # [nk, nz, 2]
+    r = torch.matmul(H, torch.matmul(H.transpose(1, 2).contiguous(), u))
+    c = torch.view_as_complex(r.contiguous()).t().reshape(g.nz, g.ny, -1)
+    return torch.fft.irfft2(c, s=(g.ny, g.nx))
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(48, 48, 608), (48, 48, 640), (64, 64, 409), (64, 64, 992), (64, 32, 641)])
+@pytest.mark.parametrize("B", [1, 2, 3, 5])
+def test_many_rows(nx, ny, nz, B):
+    op = Operator(Geometry.paper_like(nx, ny, nz, 6))
+    assert op.info()["gram_bytes"] > 256 << 20
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(nx * 10000 + nz + B)
+    z = torch.randn((B,) + op.x_shape, generator=gen, device="cuda")
+    x, zero, z0 = torch.zeros_like(z), torch.zeros_like(z), z.clone()
+    op.fista_step_normal(zero, x, z, [0.0] * B, [1.0] * B, [0.0] * B, [False] * B)   # x = z - A^T A z
+    for b in range(B):
+        ref = normal64(op, z0[b])
+        tol = 1e-5 * max(float(ref.norm()), float(z0[b].norm()))
+        assert float(((z0 - x)[b].double() - ref).norm()) <= tol, b
