@@ -406,6 +406,12 @@ __device__ __forceinline__ void stream_tile(const ContractArgs& a, int row0, int
 // and non-temporal loads stream faster (7.1 against 6.2 TB/s on a plain read
 // of 1.55 GB).  One A + one A^T: 128 x 128 x 64 x 256 (210 MB in both layouts)
 // 108 us plain, 111 non-temporal; 128 x 128 x 96 x 384 (470 MB) 187 and 174.
+// Rows that do not start at whole 64-byte pieces take plain loads at any size:
+// neighbouring tiles share a line there, and a line loaded as non-temporal
+// is often gone from the L2 when the second tile asks for it (1.2 times the
+// slab's bytes fetched at 600 values per row, 1.0 plain).  One A + one A^T,
+// non-temporal and plain: 128 x 128 x 130 x 402, 180 and 157 us; 128 x 128 x 99 x
+// 997, 314 and 258; 202 x 202 x 37 x 256 (linear) 332 and 324.
 constexpr long long kCacheBytes = 256LL << 20;
 
 // Rows from which the spectra are staged in LDS (XL).  Shorter products gain
@@ -414,7 +420,10 @@ constexpr long long kCacheBytes = 256LL << 20;
 // (192 x 192 x 100 x 229: 262.7 and 267.6 us; 256 x 256 x 128 x 512: 898 and
 // 908).  Rows of less than a tile are short runs of a slab with as many
 // spectrum bytes: staged, 202 x 202 x 37 x 256 (linear) took 640 instead of
-// 612 us.
+// 612 us.  With plain loads (above) staging pays for Gram products alone (a step
+// at 96 x 96 x 626, 384 us direct, 357 staged; 72 x 72 x 500, 168 and 157; A + A^T
+// at 96 x 96 x 131 x 517, 119 direct and 126 staged; 128 x 128 x 99 x 997, 258 and
+// 276).
 constexpr int kXlRows = 192;
 constexpr size_t kMaxLds = 160 * 1024;  // of a CU
 
@@ -468,7 +477,10 @@ static pat_status launch_u(const ContractArgs& a, dim3 grid, int TW, int KP, int
                 : wt     ? k_contract<HT, CT, U, false, true, false>
                          : k_contract<HT, CT, U, false, false, false>;
   if constexpr (CT == 1) {
-    if (xl) kernel = wt ? k_contract<HT, CT, U, true, true, true> : k_contract<HT, CT, U, true, false, true>;
+    if (xl)  // (rows of whole 16 values are whole 64 bytes: no written-through form with plain loads)
+      kernel = !nt ? k_contract<HT, CT, U, false, false, true>
+               : wt ? k_contract<HT, CT, U, true, true, true>
+                    : k_contract<HT, CT, U, true, false, true>;
   }
   kernel<<<grid, block, lds, st>>>(a, TW, KP, tgroups, pgroups, ntile);
   PAT_LAUNCHED("contraction");
@@ -488,8 +500,9 @@ static pat_status launch_t(const ContractArgs& a, hipStream_t st) {
   const long long nblk = ((long long)a.ngroup * tgroups * pgroups + 7) / 8 * 8;
   if (nblk > 0x7fffffffLL) return fail(PAT_EUNSUPPORTED, "contraction grid too large");
   const dim3 grid((unsigned)nblk);
-  const bool nt = a.reuse_bytes > kCacheBytes;
-  const bool xl = CT == 1 && nt && a.members > 2 && a.ni >= kXlRows && a.nj >= 64 && (size_t)8 * xl_stride(a.ni) <= 64 * 1024;
+  const bool big = a.reuse_bytes > kCacheBytes, nt = big && (size_t)a.s_row * sizeof(HT) % 64 == 0;
+  const bool xl = CT == 1 && (nt || (big && a.gram)) && a.members > 2 && a.ni >= kXlRows && a.nj >= 64 &&
+                  (size_t)8 * xl_stride(a.ni) <= 64 * 1024;
   const int share = (a.ni >> 3) / KP;  // row blocks of a wave
   if (CT == 1 && VEC == 4 && share % 4 == 0)
     return launch_u<HT, CT, (CT == 1 && VEC == 4 ? 4 : 2)>(a, grid, TW, KP, tgroups, pgroups, ntile, nt, xl, st);
