@@ -1,0 +1,303 @@
+// The per-frequency contraction (step (ii) of Sec. 3.2) of one object on the
+// vector units.
+//
+// Where the matrix kernel (contract.hip) is not the better one: on grids that
+// are not square, whose classes hold at most two frequencies (m, +-p), it would
+// fill a quarter of its instructions, while the vector units do the same
+// products in the time the slab takes to arrive (one A + one A^T, float32,
+// vector and matrix: 192 x 32 transforms x 54 x 476, 118 and 126 us; 96 x 108 x 95 x
+// 167, 127 and 130; 192 x 96 x 50 x 301, 197 and 205); and in Gram products
+// beyond 128 depths whose rows are not whole 128-byte lines, since here a
+// workgroup reads whole rows and meets no line twice (a step at 256 x 192 x 200,
+// 461 and 488 us; 128 x 96 x 300, 251 and 278; 96 x 96 x 300, 110 and 122).
+//
+// A slab (or, for long rows, half of every row) belongs to one workgroup: lanes
+// of a row group cover one row with 16-byte non-temporal loads, row groups take
+// interleaved rows, the member spectra sit in LDS, and an LDS tree adds the
+// row groups' sums in a fixed order.
+#include <algorithm>
+#include <type_traits>
+
+#include "contract_slab.hpp"
+#include "dft.hpp"
+#include "pat_internal.hpp"
+
+namespace pat {
+
+constexpr int kRowParts = 2;  // workgroups per slab for long rows
+template <typename HT> constexpr int kRows = std::is_same<HT, float>::value ? 2 : 4;  // rows per register buffer
+
+// One slab (or part of its rows) with GG member slots, of which grp.y are
+// filled.  Uniform per workgroup.
+template <typename HT, int GG>
+__device__ __forceinline__ void vec_group(const ContractArgs& a, int lr_log2, int4 grp, int j0, int njl,
+                                          float4* smem_raw) {
+  typedef Slab<HT> SL;
+  typedef typename SL::raw_t raw_t;
+  constexpr int VEC = SL::VEC;
+  constexpr int U = kRows<HT>;      // rows per register buffer
+  constexpr int NS = VEC * GG * 2;  // accumulators per thread
+  float2* xin = reinterpret_cast<float2*>(smem_raw);
+  float* red = reinterpret_cast<float*>(smem_raw);
+  const int tid = threadIdx.x;
+  const int Lr = 1 << lr_log2, R = 256 >> lr_log2;
+  const int lr = tid & (Lr - 1), rg = tid >> lr_log2;
+
+  // this workgroup's part of the rows: elements j0 .. j0 + njl - 1
+  const HT* slab = reinterpret_cast<const HT*>(a.slab) + (size_t)grp.z * a.slab_elems + j0;
+  const int nchunks = (njl + VEC - 1) / VEC;
+  const bool cl = lr < nchunks;
+  const HT* colp = slab + (size_t)min(lr, nchunks - 1) * VEC;  // clamped: always a valid address
+
+  // Rows in flight: the loads of the next U rows are issued before the FMAs
+  // of the current ones (two register buffers), so that every wave keeps
+  // memory requests outstanding while it computes.  Loads are unconditional
+  // (rows and chunks clamped into the slab, the value zeroed by a select) so
+  // that no branch hides them from the wait counter.
+  auto load_rows = [&](raw_t (&raw)[U], int i0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * R;
+      const int ic = min(i, a.ni - 1);
+      const raw_t v = __builtin_nontemporal_load(reinterpret_cast<const raw_t*>(colp + (size_t)ic * a.s_row));
+      raw[u] = (i < a.ni && cl) ? v : raw_t(0);
+    }
+  };
+  raw_t ra[U], rb[U];
+  load_rows(ra, rg);  // the first rows travel while the member vectors are staged
+
+  // member input vectors -> LDS xin[i][g], with the optional per-row scale;
+  // 16-byte loads along each member row when the row length is even
+  if ((a.ni & 1) == 0) {
+    // batches of kStage loads per thread, all issued before their LDS stores
+    // (one memory latency per batch instead of one per load); consecutive
+    // lanes take consecutive members of one k pair, so that the LDS stores
+    // are contiguous (the loads still cover whole 128-byte lines per wave)
+    constexpr int kStage = 8;
+    const int h = a.ni >> 1;
+    const int total = GG * h;
+    for (int base = tid; base < total; base += 256 * kStage) {
+      float4 v[kStage];
+      float2 sv[kStage];  // the per-row scales of the pair, loaded with it
+#pragma unroll
+      for (int q = 0; q < kStage; ++q) {
+        const int idx = base + q * 256;
+        v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+        sv[q] = make_float2(1.f, 1.f);
+        if (idx < total) {
+          const int g = idx % GG, i = 2 * (idx / GG);
+          if (g < grp.y) v[q] = *reinterpret_cast<const float4*>(a.in + (size_t)(grp.x + g) * a.in_rs + i);
+          if (a.in_scale) sv[q] = *reinterpret_cast<const float2*>(a.in_scale + i);
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < kStage; ++q) {
+        const int idx = base + q * 256;
+        if (idx >= total) break;
+        const int g = idx % GG, i = 2 * (idx / GG);
+        float4 w = v[q];
+        if (a.in_scale) w = make_float4(w.x * sv[q].x, w.y * sv[q].x, w.z * sv[q].y, w.w * sv[q].y);
+        xin[i * GG + g] = make_float2(w.x, w.y);
+        xin[(i + 1) * GG + g] = make_float2(w.z, w.w);
+      }
+    }
+  } else {
+    for (int idx = tid; idx < a.ni * GG; idx += 256) {
+      const int i = idx / GG, g = idx % GG;
+      float2 v = make_float2(0.f, 0.f);
+      if (g < grp.y) {
+        v = a.in[(size_t)(grp.x + g) * a.in_rs + i];
+        if (a.in_scale) v = cscale(v, a.in_scale[i]);
+      }
+      xin[idx] = v;
+    }
+  }
+  __syncthreads();
+
+  float acc[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) acc[s] = 0.f;
+
+  auto fma_rows = [&](const raw_t (&raw)[U], int i0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * R;
+      if (i >= a.ni) break;
+      float2 xv[GG];
+#pragma unroll
+      for (int g = 0; g < GG; ++g) xv[g] = xin[i * GG + g];
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) {
+        const float h = SL::get(raw[u], v);
+#pragma unroll
+        for (int g = 0; g < GG; ++g) {
+          float* p = &acc[(v * GG + g) * 2];
+          p[0] = fmaf(h, xv[g].x, p[0]);
+          p[1] = fmaf(h, xv[g].y, p[1]);
+        }
+      }
+    }
+  };
+  for (int i0 = rg; i0 < a.ni; i0 += 2 * R * U) {
+    load_rows(rb, i0 + R * U);
+    fma_rows(ra, i0);
+    if (i0 + R * U >= a.ni) break;
+    load_rows(ra, i0 + 2 * R * U);
+    fma_rows(rb, i0 + R * U);
+  }
+
+  // add the partial sums of the R row groups (fixed order: deterministic)
+  for (int half = R >> 1; half >= 1; half >>= 1) {
+    __syncthreads();
+    const int span = half * Lr;
+    if (rg >= half && rg < 2 * half) {
+      const int w = (rg - half) * Lr + lr;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) red[s * span + w] = acc[s];
+    }
+    __syncthreads();
+    if (rg < half) {
+      const int w = rg * Lr + lr;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) acc[s] += red[s * span + w];
+    }
+  }
+
+  // float32 (no scales), whole 16-byte pairs per lane and nothing to subtract:
+  // row group 0 stores its sums directly (each lane four consecutive outputs
+  // per member, the lanes of a member row contiguous), without a pass through
+  // LDS (A and A^T 1.5 % faster; the 16-bit kernels, eight outputs per lane,
+  // measured 4 % slower that way and keep the pass through LDS)
+  if (std::is_same<HT, float>::value && a.out_sub == nullptr && (a.nj & 1) == 0 && njl % VEC == 0) {
+    const int cj = lr * VEC;
+    if (rg != 0 || cj >= njl) return;
+#pragma unroll
+    for (int g = 0; g < GG; ++g) {
+      if (g >= grp.y) continue;
+      v4f* dst = reinterpret_cast<v4f*>(a.out + (size_t)(grp.x + g) * a.out_rs + j0 + cj);
+#pragma unroll
+      for (int v = 0; v < VEC; v += 2) {
+        const float* q0 = &acc[(v * GG + g) * 2];
+        const float* q1 = &acc[((v + 1) * GG + g) * 2];
+        __builtin_nontemporal_store(v4f{q0[0], q0[1], q1[0], q1[1]}, dst + v / 2);
+      }
+    }
+    return;
+  }
+
+  // stage the member rows in LDS, then store each row contiguously (whole
+  // cache lines per store instruction)
+  __syncthreads();
+  float2* ob = reinterpret_cast<float2*>(smem_raw);
+  if (rg == 0) {
+    // per-row output scales: every load issued before the first is used
+    float scv[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) scv[v] = a.out_scale ? a.out_scale[j0 + min(lr * VEC + v, njl - 1)] : 1.f;
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+      const int j = lr * VEC + v;
+      if (j >= njl) continue;
+#pragma unroll
+      for (int g = 0; g < GG; ++g) {
+        const float* p = &acc[(v * GG + g) * 2];
+        ob[g * njl + j] = make_float2(p[0] * scv[v], p[1] * scv[v]);
+      }
+    }
+  }
+  __syncthreads();
+  const size_t o0 = (size_t)grp.x * a.out_rs + j0;
+  if ((njl & 1) == 0 && (a.nj & 1) == 0) {
+    // two complex values (16 bytes) per store, non-temporal: the rows are
+    // not read again by this kernel.  kOut per thread: their values (and the
+    // subtracted ones) are all read before the first store; a load issued
+    // after a store would wait for it on the in-order memory counter
+    constexpr int kOut = 2;
+    const int h = njl >> 1;
+    for (int e0 = tid; e0 < grp.y * h; e0 += 256 * kOut) {
+      v4f d[kOut], sub[kOut];
+      size_t o[kOut];
+#pragma unroll
+      for (int q = 0; q < kOut; ++q) {
+        const int e = min(e0 + q * 256, grp.y * h - 1), g = e / h, j = 2 * (e - g * h);
+        o[q] = o0 + (size_t)g * a.out_rs + j;
+        d[q] = *reinterpret_cast<const v4f*>(ob + g * njl + j);
+        sub[q] = a.out_sub ? *reinterpret_cast<const v4f*>(a.out_sub + o[q]) : v4f(0.f);
+      }
+      // differences on straight-line code (the empty asm keeps them out of
+      // the conditional stores, where each store would wait again)
+#pragma unroll
+      for (int q = 0; q < kOut; ++q) {
+        d[q] -= sub[q];
+        asm volatile("" : "+v"(d[q]));
+      }
+#pragma unroll
+      for (int q = 0; q < kOut; ++q)
+        if (e0 + q * 256 < grp.y * h) __builtin_nontemporal_store(d[q], reinterpret_cast<v4f*>(a.out + o[q]));
+    }
+  } else {
+    for (int e = tid; e < grp.y * njl; e += 256) {
+      const int g = e / njl;
+      const size_t o = o0 + (size_t)g * a.out_rs + (e - g * njl);
+      a.out[o] = a.out_sub ? csub(ob[e], a.out_sub[o]) : ob[e];
+    }
+  }
+}
+
+// float32: two rows per register buffer instead of four, so that the kernel
+// fits 128 registers and four waves per SIMD (measured faster on short rows,
+// neutral on long ones)
+template <typename HT, int G>
+__global__ __launch_bounds__(256, (std::is_same<HT, float>::value ? 4 : 1)) void k_contract_vec(ContractArgs a,
+                                                                                               int lr_log2, int JS,
+                                                                                               int chpart) {
+  extern __shared__ float4 smem_raw[];
+  // workgroups are dealt to the eight XCDs round-robin by index: the units
+  // (group, row part) are cut into eight contiguous ranges, one per XCD
+  const int units = a.ngroup * JS;
+  const int per_xcd = (units + 7) >> 3;
+  const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (unit >= units) return;  // whole workgroup: padding of the grid
+  const int t = unit / JS, part = unit - t * JS;
+  const int4 grp = a.groups[t];  // first spectrum row, members, slab
+  constexpr int VEC = Slab<HT>::VEC;
+  const int j0 = part * chpart * VEC, njl = min(a.nj - j0, chpart * VEC);
+  if constexpr (G == 8) {
+    if (grp.y <= 4) return vec_group<HT, 4>(a, lr_log2, grp, j0, njl, smem_raw);  // the cheaper body
+  }
+  vec_group<HT, G>(a, lr_log2, grp, j0, njl, smem_raw);
+}
+
+template <typename HT, int G>
+static pat_status launch_vec(const ContractArgs& a, hipStream_t st) {
+  constexpr int VEC = Slab<HT>::VEC;
+  // rows of 128 or more 16-byte chunks are split over kRowParts workgroups
+  // per slab (halves of 1 KB and more still stream well; shorter parts
+  // measured slower)
+  const int chunks = (a.nj + VEC - 1) / VEC;
+  const int JS = chunks >= 128 ? kRowParts : 1;
+  const int chpart = (chunks + JS - 1) / JS;  // 16-byte chunks per part
+  if (chpart > 256) return fail(PAT_EUNSUPPORTED, "contraction row longer than 512 vectors");
+  int lr_log2 = 0;
+  while ((1 << lr_log2) < chpart) ++lr_log2;
+  const int Lr = 1 << lr_log2, R = 256 / Lr;
+  const size_t red_bytes = R > 1 ? (size_t)(R / 2) * Lr * VEC * G * 2 * sizeof(float) : 0;
+  const size_t in_bytes = (size_t)a.ni * G * sizeof(float2);
+  const size_t out_bytes = (size_t)chpart * VEC * G * sizeof(float2);
+  const size_t lds = std::max(red_bytes, std::max(in_bytes, out_bytes));
+  if (lds > 160 * 1024) return fail(PAT_EUNSUPPORTED, "contraction input vector does not fit in LDS");
+  const long long nblk = ((long long)a.ngroup * JS + 7) / 8 * 8;
+  if (nblk > 0x7fffffffLL) return fail(PAT_EUNSUPPORTED, "contraction grid too large");
+  k_contract_vec<HT, G><<<dim3((unsigned)nblk), 256, lds, st>>>(a, lr_log2, JS, chpart);
+  PAT_LAUNCHED("contraction (vector units)");
+  return PAT_OK;
+}
+
+pat_status contract_vec(const ContractArgs& a, int hdtype, hipStream_t st) {
+  if (a.B != 1) return fail(PAT_EINVAL, "the vector contraction takes one object");
+  if (hdtype == PAT_H_F32) return a.members > 2 ? launch_vec<float, 8>(a, st) : launch_vec<float, 2>(a, st);
+  if (a.members > 2 || a.out_sub) return fail(PAT_EINVAL, "the vector contraction of 16-bit slabs: two members");
+  return hdtype == PAT_H_BF16 ? launch_vec<bf16_t, 2>(a, st) : launch_vec<f16_t, 2>(a, st);
+}
+
+}  // namespace pat

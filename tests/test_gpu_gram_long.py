@@ -37,3 +37,34 @@ def test_many_rows(nx, ny, nz, B):
         ref = normal64(op, z0[b])
         tol = 1e-5 * max(float(ref.norm()), float(z0[b].norm()))
         assert float(((z0 - x)[b].double() - ref).norm()) <= tol, b
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(72, 72, 373), (72, 72, 374), (128, 128, 217), (96, 64, 262), (48, 32, 1030), (64, 32, 777)])
+def test_broken_lines(nx, ny, nz):
+    # blocks whose rows are not whole 128-byte lines: one object on the vector
+    # units, with classes of eight and of two members, odd and even rows, rows
+    # over one and two workgroups, with and without the subtracted spectrum
+    op = Operator(Geometry.paper_like(nx, ny, nz, 6))
+    i = op.info()
+    assert i["gram_bytes"] > 256 << 20
+    H = op.export_H().double()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(nx * 10000 + nz)
+    z0 = torch.randn(op.x_shape, generator=gen, device="cuda")
+    z, x, zero = z0[None].clone(), torch.zeros_like(z0)[None], torch.zeros_like(z0)[None]
+    op.fista_step_normal(zero, x, z, [0.0], [1.0], [0.0], [False])   # x = z - A^T A z
+    ref = normal64(op, z0)
+    assert float(((z0 - x[0]).double() - ref).norm()) <= 1e-5 * max(float(ref.norm()), float(z0.norm()))
+
+    d = torch.randn(op.d_shape, generator=gen, device="cuda")
+    u = torch.view_as_real(torch.fft.rfft2(d.double()).reshape(op.geom.nt, -1).t().contiguous())
+    c = torch.view_as_complex(torch.matmul(H, u).contiguous()).t().reshape(nz, ny, -1)
+    b, tau = torch.fft.irfft2(c, s=(ny, nx)), 0.25
+    xk, zk, t = torch.zeros_like(b), torch.zeros_like(b), 1.0
+    for _ in range(3):
+        v = zk - tau * (normal64(op, zk) - b)
+        tn = (1.0 + (1.0 + 4.0 * t * t) ** 0.5) / 2.0
+        xn = v.clamp_min(0.0)
+        zk, xk, t = xn + (t - 1.0) / tn * (xn - xk), xn, tn
+    got = op.recon_fista(d, 3, tau, 0.0, nonneg=True).double()
+    assert float((got - xk).norm()) <= 1e-5 * float(xk.norm())
