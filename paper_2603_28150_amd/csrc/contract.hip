@@ -76,13 +76,14 @@ __host__ __device__ __forceinline__ int xl_stride(int ni) { return (ni * 8 + 255
 // (where they are long and come from memory, reading them piecewise between
 // the slab loads costs more than the barrier).  NT: non-temporal slab loads.
 // WT: output lines are written through.
-template <typename HT, int CT, int U, bool NT, bool WT, bool XL>
+template <typename HT, int V, int CT, int U, bool NT, bool WT, bool XL>
 __device__ __forceinline__ void stream_tile(const ContractArgs& a, int row0, int slab_id, int tile, int kpart, int KP,
                                             int pg0, int np, float* red) {
-  typedef Slab<HT> SL;
+  typedef Slab<HT, V> SL;
   typedef typename SL::raw_t raw_t;
-  constexpr int VEC = SL::VEC;
+  constexpr int VEC = V;
   constexpr unsigned ESZ = sizeof(HT);
+  constexpr bool SCALED = ESZ == 2;  // 16-bit libraries have scales
   const int lane = threadIdx.x & 63;
   const int c = lane >> 4, l16 = lane & 15;
   int ls = 0;  // log2 S
@@ -128,7 +129,7 @@ __device__ __forceinline__ void stream_tile(const ContractArgs& a, int row0, int
   struct Buf {
     raw_t h[U][2];
     v4f x[U][CT];
-    float2 sc[VEC == 8 ? U : 1];
+    float2 sc[SCALED ? U : 1];
   };
   // keeps a 32-bit offset next to its load (widened in advance, it would take
   // two registers and a 64-bit addition per load)
@@ -155,7 +156,7 @@ __device__ __forceinline__ void stream_tile(const ContractArgs& a, int row0, int
 #pragma unroll
         for (int m = 0; m < CT; ++m) o.x[u][m] = *reinterpret_cast<const v4f8*>(px + here(xv[m]));
       }
-      if constexpr (VEC == 8)
+      if constexpr (SCALED)
         o.sc[u] = a.in_scale ? *reinterpret_cast<const float2*>(a.in_scale + ((size_t)bb << lb) + rl)
                              : make_float2(1.f, 1.f);
     }
@@ -196,7 +197,7 @@ __device__ __forceinline__ void stream_tile(const ContractArgs& a, int row0, int
 #pragma unroll
       for (int m = 0; m < CT; ++m) {
         xs[m] = im ? x[m][2 * s + 1] : x[m][2 * s];
-        if constexpr (VEC == 8) xs[m] *= s ? sc.y : sc.x;
+        if constexpr (SCALED) xs[m] *= s ? sc.y : sc.x;
       }
 #pragma unroll
       for (int v = 0; v < VEC; ++v) {
@@ -211,8 +212,8 @@ __device__ __forceinline__ void stream_tile(const ContractArgs& a, int row0, int
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (b + u >= b1) break;
-      mma_block(o.h[u], o.x[u], o.sc[VEC == 8 ? u : 0]);
-      if (u % 2 == 1 || (VEC == 4 && CT == 1 && U == 2)) flush();
+      mma_block(o.h[u], o.x[u], o.sc[SCALED ? u : 0]);
+      if (u % 2 == 1 || (ESZ == 4 && CT == 1 && U == 2)) flush();
     }
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -232,7 +233,7 @@ __device__ __forceinline__ void stream_tile(const ContractArgs& a, int row0, int
 #pragma unroll
     for (int m = 0; m < CT; ++m)
       tx[m] = *reinterpret_cast<const v4f8*>(xb + (xv[m] - rl * 8u) + (unsigned)x0 * 8u);
-    if (VEC == 8 && a.in_scale)
+    if (SCALED && a.in_scale)
       tsc = make_float2(a.in_scale[min(r0, a.ni - 1)], a.in_scale[min(r0 + 1, a.ni - 1)]);
   }
   Buf ba, bb;
@@ -322,8 +323,8 @@ __device__ __forceinline__ void stream_tile(const ContractArgs& a, int row0, int
   // Accumulator row r of lane group c holds a part of pair 2c + r/2 (re, im), at output n + v for instruction v.  The tile goes
   // through the wave's own part of LDS so that each store instruction writes
   // whole runs of a spectrum row instead of half of every 32 bytes.
-  constexpr int NU = VEC;                       // 16-byte units per lane
-  constexpr int lu = VEC == 8 ? 6 : 5;          // log2 units of a row (tn / 2)
+  constexpr int NU = VEC;                              // 16-byte units per lane
+  constexpr int lu = VEC == 8 ? 6 : VEC == 4 ? 5 : 4;  // log2 units of a row (tn / 2)
   float* tr = red + (size_t)w * (KP > 1 ? CT : 1) * VEC * 256;
   const size_t obase = (size_t)row0 * a.out_rs;
   const auto orow = __builtin_amdgcn_make_buffer_rsrc(a.out + obase, (short)0, 8 * a.out_rs * 8, 0x00020000);
@@ -427,7 +428,7 @@ constexpr long long kCacheBytes = 256LL << 20;
 constexpr int kXlRows = 192;
 constexpr size_t kMaxLds = 160 * 1024;  // of a CU
 
-template <typename HT, int CT, int U, bool NT, bool WT, bool XL>
+template <typename HT, int V, int CT, int U, bool NT, bool WT, bool XL>
 __global__ __launch_bounds__(256, (CT > 1 ? 2 : 3)) void k_contract(ContractArgs a, int TW, int KP, int tgroups,
                                                                      int pgroups, int ntile) {
   extern __shared__ float red[];
@@ -443,19 +444,18 @@ __global__ __launch_bounds__(256, (CT > 1 ? 2 : 3)) void k_contract(ContractArgs
   const int kpart = w % KP, tile = min(tg * TW + w / KP, ntile);  // tile ntile: no outputs (idle wave)
   if (!XL && KP == 1 && tile == ntile) return;
   if constexpr (CT == 4) {  // few pairs left: the cheaper bodies
-    if (np - pg0 <= 8) return stream_tile<HT, 1, 2, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
-    if (np - pg0 <= 16) return stream_tile<HT, 2, 2, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
+    if (np - pg0 <= 8) return stream_tile<HT, V, 1, 2, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
+    if (np - pg0 <= 16) return stream_tile<HT, V, 2, 2, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
   }
   if constexpr (CT == 2) {
-    if (np - pg0 <= 8) return stream_tile<HT, 1, 2, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
+    if (np - pg0 <= 8) return stream_tile<HT, V, 1, 2, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
   }
-  stream_tile<HT, CT, U, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
+  stream_tile<HT, V, CT, U, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
 }
 
-template <typename HT, int CT, int U>
+template <typename HT, int V, int CT, int U>
 static pat_status launch_u(const ContractArgs& a, dim3 grid, int TW, int KP, int tgroups, int pgroups, int ntile, bool nt,
                      bool xl, hipStream_t st) {
-  constexpr int VEC = Slab<HT>::VEC;
   // Written-through lines (whole 128-byte lines only: parts of lines made the
   // launch up to twice as slow) where little is written per slab byte: mixing
   // writes into the slab stream costs more than their bytes (1.55 GB read in
@@ -469,44 +469,70 @@ static pat_status launch_u(const ContractArgs& a, dim3 grid, int TW, int KP, int
   // leave room for one workgroup per CU from 289 rows on (a step of 4 and 16
   // objects at 64 x 64 x 512: 222 and 986 us with that much LDS, 216 and 881
   // without) and for none beyond 608
-  const size_t lds = std::max((size_t)TW * KP * (KP > 1 ? CT : 1) * VEC * 256 * sizeof(float),
+  const size_t lds = std::max((size_t)TW * KP * (KP > 1 ? CT : 1) * V * 256 * sizeof(float),
                               xl ? (size_t)8 * xl_stride(a.ni) : 0);
   if (lds > kMaxLds) return fail(PAT_EUNSUPPORTED, "contraction: sums and spectra do not fit in LDS");
-  auto kernel = nt && wt ? k_contract<HT, CT, U, true, true, false>
-                : nt     ? k_contract<HT, CT, U, true, false, false>
-                : wt     ? k_contract<HT, CT, U, false, true, false>
-                         : k_contract<HT, CT, U, false, false, false>;
-  if constexpr (CT == 1) {
+  auto kernel = nt && wt ? k_contract<HT, V, CT, U, true, true, false>
+                : nt     ? k_contract<HT, V, CT, U, true, false, false>
+                : wt     ? k_contract<HT, V, CT, U, false, true, false>
+                         : k_contract<HT, V, CT, U, false, false, false>;
+  if constexpr (CT == 1 && V * sizeof(HT) == 16) {
     if (xl)  // (rows of whole 16 values are whole 64 bytes: no written-through form with plain loads)
-      kernel = !nt ? k_contract<HT, CT, U, false, false, true>
-               : wt ? k_contract<HT, CT, U, true, true, true>
-                    : k_contract<HT, CT, U, true, false, true>;
+      kernel = !nt ? k_contract<HT, V, CT, U, false, false, true>
+               : wt ? k_contract<HT, V, CT, U, true, true, true>
+                    : k_contract<HT, V, CT, U, true, false, true>;
   }
   kernel<<<grid, block, lds, st>>>(a, TW, KP, tgroups, pgroups, ntile);
   PAT_LAUNCHED("contraction");
   return PAT_OK;
 }
 
-template <typename HT, int CT>
+constexpr int kFewGroups = 3 * 256;  // three workgroups per CU
+
+template <typename HT, int V, int CT>
 static pat_status launch_t(const ContractArgs& a, hipStream_t st) {
-  constexpr int VEC = Slab<HT>::VEC;
   // four waves per workgroup: one per tile up to four tiles; with one or two
   // tiles, four or two waves share the rows of each
-  constexpr int tn = 16 * VEC;
+  constexpr int tn = 16 * V;
   const int ntile = (a.nj + tn - 1) / tn;
-  const int tgroups = (ntile + 3) / 4, TW = (ntile + tgroups - 1) / tgroups;
-  const int KP = TW == 1 ? 4 : TW == 2 ? 2 : 1;
+  int tgroups = (ntile + 3) / 4, TW = (ntile + tgroups - 1) / tgroups;
+  int KP = TW == 1 ? 4 : TW == 2 ? 2 : 1;
   const int pgroups = (a.members * a.B + 8 * CT - 1) / (8 * CT);
+  // 16-bit slabs keep the matrix cores as busy as the loads: with fewer than
+  // three workgroups per CU some CUs would have half of the others' work.  One
+  // tile per workgroup, its rows shared by the four waves, evens that out (A,
+  // bf16: 32 x 32 x 1024 x 1024, 90 us and 65 so; 48 x 48 x 700 x 700, 91 and 69;
+  // float32, bound by the loads, is better left: A^T at 64 x 64 x 256 x 1024, 82
+  // and 86)
+  if (sizeof(HT) == 2 && (KP == 1 || V == 4) && (long long)a.ngroup * tgroups < kFewGroups && a.ni >= 256) {
+    KP = 4;
+    TW = 1;
+    tgroups = ntile;
+  }
   const long long nblk = ((long long)a.ngroup * tgroups * pgroups + 7) / 8 * 8;
   if (nblk > 0x7fffffffLL) return fail(PAT_EUNSUPPORTED, "contraction grid too large");
   const dim3 grid((unsigned)nblk);
   const bool big = a.reuse_bytes > kCacheBytes, nt = big && (size_t)a.s_row * sizeof(HT) % 64 == 0;
-  const bool xl = CT == 1 && (nt || (big && a.gram)) && a.members > 2 && a.ni >= kXlRows && a.nj >= 64 &&
-                  (size_t)8 * xl_stride(a.ni) <= 64 * 1024;
+  const bool xl = CT == 1 && V * sizeof(HT) == 16 && (nt || (big && a.gram)) && a.members > 2 && a.ni >= kXlRows &&
+                  a.nj >= 64 && (size_t)8 * xl_stride(a.ni) <= 64 * 1024;
   const int share = (a.ni >> 3) / KP;  // row blocks of a wave
-  if (CT == 1 && VEC == 4 && share % 4 == 0)
-    return launch_u<HT, CT, (CT == 1 && VEC == 4 ? 4 : 2)>(a, grid, TW, KP, tgroups, pgroups, ntile, nt, xl, st);
-  return launch_u<HT, CT, (CT == 4 ? 1 : 2)>(a, grid, TW, KP, tgroups, pgroups, ntile, nt, xl, st);
+  constexpr int U4 = CT == 1 && V <= 4 ? 4 : 2;
+  if (CT == 1 && V <= 4 && share % 4 == 0)
+    return launch_u<HT, V, CT, U4>(a, grid, TW, KP, tgroups, pgroups, ntile, nt, xl, st);
+  return launch_u<HT, V, CT, (CT == 4 ? 1 : 2)>(a, grid, TW, KP, tgroups, pgroups, ntile, nt, xl, st);
+}
+
+// 16-bit rows: a tile of 16-byte loads is 128 outputs, and a matrix instruction
+// is issued per value of a load whether its columns are outputs or not.  Rows
+// of up to a half or a quarter of that take 8- or 4-byte loads (A^T, bf16, 16-
+// byte loads and these: 216 x 216 x 5 x 1670, 250 and 92 us; 64 x 64 x 1100 x 48 (A),
+// 29 and 20), and one tile's rows two tiles of 8-byte loads where the groups
+// are few (72 x 72 x 127 x 992, A^T: 47 and 35).
+template <typename HT>
+static pat_status launch_16(const ContractArgs& a, hipStream_t st) {
+  if (a.nj <= 32) return launch_t<HT, 2, 1>(a, st);
+  if (a.nj <= 64 || (a.nj <= 128 && a.ngroup < kFewGroups)) return launch_t<HT, 4, 1>(a, st);
+  return launch_t<HT, 8, 1>(a, st);
 }
 
 // Gram products that the vector units' kernel takes: of one object, from HBM, of
@@ -540,12 +566,12 @@ pat_status contract(const ContractArgs& a, int hdtype, hipStream_t st) {
   const long long units = (long long)a.ngroup * ((a.members * a.B + 7) / 8);
   if (a.gram && (a.ni <= 64 || (a.ni <= 128 && (a.B > 1 || a.s_row % 16 == 0) && units >= 1024)))
     return contract_sym(a, a.reuse_bytes > kCacheBytes, st);
-  if (hdtype == PAT_H_BF16) return launch_t<bf16_t, 1>(a, st);
-  if (hdtype == PAT_H_F16) return launch_t<f16_t, 1>(a, st);
+  if (hdtype == PAT_H_BF16) return launch_16<bf16_t>(a, st);
+  if (hdtype == PAT_H_F16) return launch_16<f16_t>(a, st);
   const int pairs = a.members * a.B;
-  if (pairs <= 8) return launch_t<float, 1>(a, st);
-  if (pairs <= 16) return launch_t<float, 2>(a, st);
-  return launch_t<float, 4>(a, st);
+  if (pairs <= 8) return launch_t<float, 4, 1>(a, st);
+  if (pairs <= 16) return launch_t<float, 4, 2>(a, st);
+  return launch_t<float, 4, 4>(a, st);
 }
 
 }  // namespace pat

@@ -26,12 +26,8 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("n,nz,nt,kind", CASES)
-@pytest.mark.parametrize("adjoint", [False, True])
-def test_contraction_of_large_libraries(n, nz, nt, kind, adjoint):
-    op = Operator(Geometry.paper_like(n, n, nz, nt), kind)
-    i = op.info()
-    assert 2 * min(i["slab_bytes_A"], i["slab_bytes_AT"]) > 256 << 20
+def check_contraction(op, adjoint, blocks):
+    nz, nt = op.geom.nz, op.geom.nt
     K, N = (nt, nz) if adjoint else (nz, nt)
     rows = torch.tensor(op.spectrum_rows(), device="cuda")
     used = torch.nonzero(rows >= 0)[:, 0]
@@ -45,13 +41,33 @@ def test_contraction_of_large_libraries(n, nz, nt, kind, adjoint):
     assert torch.isfinite(out[used][:, :N]).all()
     row_of = torch.empty(op.nk, dtype=torch.long, device="cuda")
     row_of[rows[used].long()] = used
-    for k0 in (0, 1, op.nk // 3 - 7, op.nk // 2, op.nk - 40):
+    for k0 in blocks:
         H = op.export_H(k0, 40).double()                             # [40, nz, nt]
         M = H if adjoint else H.transpose(1, 2).contiguous()
         r = row_of[k0:k0 + 40]
         x = spec[r][:, :K].double().contiguous()
         err = (out[r][:, :N].double() - torch.matmul(M, x)).abs()
         assert (err <= (K + 4) * 2.0 ** -24 * torch.matmul(M.abs(), x.abs())).all(), (k0, float(err.max()))
+
+
+@pytest.mark.parametrize("n,nz,nt,kind", CASES)
+@pytest.mark.parametrize("adjoint", [False, True])
+def test_contraction_of_large_libraries(n, nz, nt, kind, adjoint):
+    op = Operator(Geometry.paper_like(n, n, nz, nt), kind)
+    i = op.info()
+    assert 2 * min(i["slab_bytes_A"], i["slab_bytes_AT"]) > 256 << 20
+    check_contraction(op, adjoint, (0, 1, op.nk // 3 - 7, op.nk // 2, op.nk - 40))
+
+
+# 16-bit rows of up to 32, 64, 128 and more values (loads of 4, 8 and 16 bytes),
+# long sums shared by the waves of a workgroup, ends inside a block of rows
+@pytest.mark.parametrize("nz,nt", [(260, 391), (257, 129), (300, 31), (32, 303), (512, 64), (33, 1100), (128, 777), (2, 263)])
+@pytest.mark.parametrize("kind", ["bf16", "f16"])
+@pytest.mark.parametrize("n", [16, 48])
+def test_contraction_of_16_bit_rows(n, nz, nt, kind):
+    op = Operator(Geometry.paper_like(n, n, nz, nt), kind)
+    for adjoint in (False, True):
+        check_contraction(op, adjoint, range(0, op.nk - 39, 40 if n == 16 else 400))
 
 
 @pytest.mark.parametrize("n,nz,B", [(256, 113, 1), (256, 113, 2), (256, 127, 1), (512, 62, 1), (256, 121, 3)])
