@@ -637,16 +637,24 @@ static bool extents_ok(int fx, int fy, int nxw, int nyw, int sx, int sy) {
 
 // Grids and slice counts that one kernel transforms (k_fft_small_*): both axes
 // of 16 to 64 points (the grid fits a workgroup's LDS several times per CU),
-// every sample, at most 4 M values.  Up to there two passes are bound by their
-// launches and their latency, beyond it by bytes, and then whole lines along
-// the slices are the better access.  One forward and one inverse transform,
-// two passes and one: 32 x 32, 512 slices 23.0 and 17.4 us, 4,096 slices (4 M)
-// 37.7 and 32.0; 64 x 64, 512 slices 29.3 and 20.1, 1,024 (4 M) 36.0 and 35.0,
-// 2,048 53.1 and 63.7; 48 x 48, 1,024 slices 30.4 and 21.9, 2,048 (4.7 M) 37.8
-// and 46.2.
-static bool small_grid(int fx, int fy, int sx, int sy, int S) {
+// every sample, and as many values as the launches and their latency bound the
+// two passes; beyond, bytes do, and whole lines along the slices are the better
+// access (the forward kernel writes 16-byte pieces of them).  One apply of few
+// depths whose data side takes two passes and one kernel, inverse (A) / forward
+// (A^T) us gained: 32 x 32, 4,096 slices (4 M) 7.6 / 0.0; 48 x 32, 1,536 (2.25 M) 4.5 /
+// 1.6, 1,791 (2.6 M) 3.2 / -1.1; 64 x 32, 2,048 (4 M) 7.5 / 1.2, 1,791 4.4 / -1.3;
+// 48 x 48, 1,024 (2.25 M) 5.3 / 1.9, 1,280 (2.8 M) 0.9 / -3.0, 1,791 (3.9 M) -4.4 / -4.7;
+// 64 x 48, 1,024 (3 M) 4.8 / -2.3, 1,100 (3.2 M) -2.5 / -5.0; 64 x 64, 512 (2 M) 5.9 / 0.4,
+// 768 (3 M) -0.9 / -4.8 (one A + one A^T of three objects there, 64 depths and 256
+// samples each: 75 us with two passes at 768 slices, 83 with one kernel).
+static bool small_grid(int fx, int fy, int sx, int sy, int S, bool inverse) {
   auto ok = [](int n) { return n == 16 || n == 32 || n == 48 || n == 64; };
-  return ok(fx) && ok(fy) && sx == 1 && sy == 1 && (long long)S * fx * fy <= (1LL << 22);
+  if (!ok(fx) || !ok(fy) || sx != 1 || sy != 1) return false;
+  const int area = fx * fy;
+  const long long most = area <= 1024 || (inverse && area <= 2048) ? 4LL << 20
+                         : inverse && area <= 3072                ? 3LL << 20
+                                                                  : 9LL << 18;
+  return (long long)S * area <= most;
 }
 
 template <typename F>
@@ -677,7 +685,7 @@ pat_status fft2_r2c(const float* f, float2* T, float2* X, int fx, int fy, int nx
   const int nxc = nxw / sx, nyc = nyw / sy;
   if ((dn.tx && (nxw != fx || sx != 1)) || (dn.ty && (nyw != fy || sy != 1)))
     return fail(PAT_EUNSUPPORTED, "fft: axes without a fast transform take whole, unsampled slices");
-  if (small_grid(fx, fy, sx, sy, S)) {
+  if (small_grid(fx, fy, sx, sy, S, false)) {
     small_dispatch(fx, fy, [&](auto nx, auto ny) {
       constexpr int NX = decltype(nx)::value, NY = decltype(ny)::value;
       k_fft_small_r2c<NX, NY><<<small_blocks(S), SmallGrid<NX, NY>::NT, 0, st>>>(f, X, nyc, nxc, S, rs, rowmap);
@@ -715,7 +723,7 @@ pat_status fft2_c2r(const float2* X, float2* T, float* f, int fx, int fy, int nx
   const int nxc = nxw / sx, nyc = nyw / sy;
   if ((dn.tx && (nxw != fx || sx != 1)) || (dn.ty && (nyw != fy || sy != 1)))
     return fail(PAT_EUNSUPPORTED, "fft: axes without a fast transform take whole, unsampled slices");
-  if (small_grid(fx, fy, sx, sy, S)) {
+  if (small_grid(fx, fy, sx, sy, S, true)) {
     small_dispatch(fx, fy, [&](auto nx, auto ny) {
       constexpr int NX = decltype(nx)::value, NY = decltype(ny)::value;
       k_fft_small_c2r<NX, NY><<<small_blocks(S), SmallGrid<NX, NY>::NT, 0, st>>>(X, f, nyc, nxc, S, rs, scale, sub,
