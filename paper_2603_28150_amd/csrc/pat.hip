@@ -257,6 +257,14 @@ static Classes make_classes(const pat_geometry& g) {
   }
   C.kclass.assign(nk, -1);
   C.rowmap.assign(nk, -1);
+  size_t nitem = 0, ngroup = 0;
+  for (const auto& mem : groups) {
+    nitem += (mem.size() + C.G - 1) / C.G;
+    ngroup += (mem.size() + kGroup - 1) / kGroup;
+  }
+  C.item_slab.reserve(nitem);
+  C.members.reserve(nitem * C.G);
+  C.groups.reserve(ngroup);
   for (int gi = 0; gi < (int)groups.size(); ++gi) {
     const auto& mem = groups[gi];
     // items are filled in order, so a class's rows are consecutive
