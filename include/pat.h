@@ -167,9 +167,10 @@ pat_status pat_H_export(pat_op* op, int32_t k0, int32_t nk, float* out, void* st
  * slabs (symmetry classes: frequencies with equal kx^2 + ky^2 share one), the
  * z-period used, and the bytes of one stored row layout (the library keeps
  * two, rows along n for A and along l for A^T; a 16-bit library also keeps
- * both as matrix-core operand tiles, padded to 32 x 16, for batches).  The
- * contraction runs over nitems work items of up to members_max frequencies;
- * each streams one slab, so one apply of one object reads read_bytes_A (or
+ * both as matrix-core operand tiles, padded to 32 x 16, for batches).  A
+ * batched contraction runs over nitems work items of up to members_max
+ * frequencies, one slab each; the contraction of one object takes the
+ * frequencies of a class by eights, so that its apply reads read_bytes_A (or
  * read_bytes_AT) of library.  gram_bytes: the Gram blocks kept for the
  * normal-operator gradient (one nz x nz float32 block per class), 0 when the
  * library has none (see pat_recon_fista). */

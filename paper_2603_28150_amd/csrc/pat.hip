@@ -197,14 +197,14 @@ static pat_status check_geometry(const pat_geometry* g) {
 // whole symmetry class of half-spectrum frequencies:
 //   quadrant fold (any grid):          (|m~|, |p~|), <= 2 members
 //   radial fold (nx = ny, dx = dy):    all frequencies with equal m~^2 + p~^2
-// A work item of the contraction is one slab with up to G member
+// A work item of the batched contraction is one slab with up to G member
 // frequencies (a class with more members than G is split into several items
 // that read the same slab, adjacent in item order, so that the contraction
 // runs them on one XCD and the second read hits its L2); its members occupy
 // spectrum rows item*G .. item*G+G-1.  G = 8 for float32 libraries; 16-bit
 // libraries take G = 4 so that a batch of 16 objects (64 member-object
-// pairs) stays in two matrix-core column groups of 32 pairs, and the VALU
-// kernel (8 values per 16-byte load) keeps its accumulators in registers.
+// pairs) stays in two matrix-core column groups of 32 pairs.  One object and
+// the Gram products take the members by eights whatever G is (groups).
 struct Classes {
   int G = 2;
   std::vector<int32_t> freq;       // [nslab][2] representative |m~|, |p~|
@@ -312,9 +312,9 @@ static HLayout h_layout(const pat_geometry& g, const Classes& C) {
   L.ksA = (g.nz + 15) / 16;
   L.ntT = (g.nz + 31) / 32;
   L.ksT = (g.nt + 15) / 16;
-  // rows [slab][l][n] and [slab][n][l] of the storage type, for the VALU
-  // contraction; 16-bit libraries add both layouts as MFMA fragments for
-  // batches (the FP32 rows serve every batch size)
+  // rows [slab][l][n] and [slab][n][l] of the storage type, for the
+  // contraction of one object; 16-bit libraries add both layouts as MFMA
+  // fragments for batches (the FP32 rows serve every batch size)
   L.bytes_Ar = (size_t)L.nclass * g.nz * L.sA_row * esz;
   L.bytes_Tr = (size_t)L.nclass * g.nt * L.sT_row * esz;
   if (g.h_dtype == PAT_H_F32) {
@@ -449,10 +449,9 @@ static pat_status run_contract(pat_op* op, bool adjoint, const float2* in, float
   a.B = B;
   a.members = op->G > 2 ? kGroup : 2;
   const float* sc = g.h_dtype == PAT_H_F32 ? nullptr : op->inv_scale;
-  // one object: the VALU kernel on the row layouts streams the library at
-  // the FP32 kernel's rate; batches go to the matrix cores (one slab read
-  // serves every object; FP32 values enter as two float16 terms, scaled by
-  // a power of two per row)
+  // one object: the row layouts, multiplied in float32; batches: matrix
+  // instructions of 16 bits (one slab read serves every object; FP32 values
+  // enter as two float16 terms, scaled by a power of two per row)
   const bool f32 = g.h_dtype == PAT_H_F32;
   if (B > 1) {
     MfmaArgs m;
@@ -872,8 +871,8 @@ pat_status pat_get_info(const pat_op* op, pat_op_info* info) {
   info->slab_bytes_A = L.bytes_Ar;
   info->slab_bytes_AT = L.bytes_Tr;
   info->nitems = op->nitem;
-  info->read_bytes_A = L.bytes_Ar / op->nclass * op->nitem;
-  info->read_bytes_AT = L.bytes_Tr / op->nclass * op->nitem;
+  info->read_bytes_A = L.bytes_Ar / op->nclass * op->ngroup;
+  info->read_bytes_AT = L.bytes_Tr / op->nclass * op->ngroup;
   info->spec_rows = op->nrows;
   info->gram_bytes = L.bytes_G;
   return PAT_OK;
