@@ -13,23 +13,21 @@
 // The product runs on the float32 matrix instruction v_mfma_f32_16x16x4_f32:
 // its 16 rows are the real and imaginary parts of 8 pairs, its 16 columns are
 // outputs, 4 slab rows are summed per instruction, all in float32.  A wave owns
-// a tile of 16 VEC outputs (VEC values per 16-byte load) and streams its slab
+// a tile of 16 VEC outputs (VEC values per load, 16 bytes of them as a rule) and streams its slab
 // rows straight into the operand registers, VEC instructions per load: no
 // barrier and no sum across lanes, so that a wave only ever waits for its own
 // loads, and no vector arithmetic beside the matrix instructions (a load costs
 // one issue slot: scalar block base plus a fixed lane offset).
 //
-// Bound by HBM at full size, by latency below: the vector kernel this replaced
-// (one workgroup per slab, spectra in LDS, an LDS tree over the row groups)
-// took, per launch of A / A^T: 32 x 32 x 16 x 64, 9.7 / 11 us, now 4 / 4 (the
-// tree was six levels deep); 128 x 128 x 96 x 384, 53 / 57, now 50 / 47;
-// 202 x 202 x 37 x 256 on 432 x 432, 171 / 221, now 144 / 157; 256 x 256 x
-// 128 x 512, 307 / 287, now 300 / 277 (5.9 TB/s); with bf16 slabs 195 / 200,
-// now 179 / 164 (groups of 8 members read a slab once that two items of 4
-// read twice).  FISTA's Gram products (of more than 128 rows, or of one object
-// with rows not of whole 64 bytes; contract_sym.hip takes the others) of 4 objects
-// (two to four pairs of columns per value loaded), per step: 256 x 256 x 128,
-// 590 us, 484 with this; 128 x 128 x 96, 121 and 95.
+// Bound by HBM at full size, by latency below.  The vector kernel this replaced
+// (one workgroup per slab, spectra in LDS, an LDS tree over the row groups), per
+// launch of A / A^T under the profiler, and this: 32 x 32 x 16 x 64, 9.9 / 12.7 us,
+// now 4.3 / 4.6 (the tree was six levels deep); 128 x 128 x 96 x 384, 55 / 59, now
+// 55 / 52; 202 x 202 x 37 x 256 on 432 x 432, 171 / 243, now 146 / 194; 256 x 256 x
+// 128 x 512, 308 / 307, now 308 / 311 (5.6 TB/s of slabs and spectra); with bf16
+// slabs 186 / 204, now 182 / 181 (groups of 8 members read a slab once that two
+// items of 4 read twice).  contract() says which products go to the half-block
+// kernel (contract_sym.hip) and the vector units (contract_vec.hip) instead.
 #include <algorithm>
 #include <type_traits>
 
@@ -395,13 +393,6 @@ __device__ __forceinline__ void stream_tile(const ContractArgs& a, int row0, int
   }
 }
 
-// Workgroup = TW tiles x KP row shares of one (item, tile group, pair group).
-// Workgroups are dealt to the eight XCDs round-robin by index, so the units,
-// in item order, are cut into eight contiguous ranges, one per XCD, each taken
-// in order: the pair groups of an item, and the items a large class is split
-// into (adjacent, reading the same slab), run on one XCD at about the same
-// time, and every read of a slab after the first comes from that XCD's L2
-// instead of HBM.
 // Slabs that come round again before this much else has been read stay in the
 // memory-side cache (256 MB) with plain loads; a larger working set streams,
 // and non-temporal loads stream faster (7.1 against 6.2 TB/s on a plain read
@@ -415,11 +406,14 @@ __device__ __forceinline__ void stream_tile(const ContractArgs& a, int row0, int
 // 997, 314 and 258; 202 x 202 x 37 x 256 (linear) 332 and 324.
 constexpr long long kCacheBytes = 256LL << 20;
 
-// Rows from which the spectra are staged in LDS (XL).  Shorter products gain
+// Rows from which the spectra are staged in LDS (XL; float32 slabs: with 16-bit
+// ones, busier on the matrix cores, the barrier costs more than it saves: one A +
+// one A^T at 256 x 256 x 128 x 208, bf16, 363 us staged and 342 direct; 192 x 192 x 96 x
+// 384, 282 and 275).  Shorter products gain
 // nothing from it (A^T of 128 x 128 x 64 x 256: 22.5 us direct, 25.4 staged);
-// at 229 and 512 rows the pair of applies is 2 % and 1 % faster staged
-// (192 x 192 x 100 x 229: 262.7 and 267.6 us; 256 x 256 x 128 x 512: 898 and
-// 908).  Rows of less than a tile are short runs of a slab with as many
+// longer ones 1 to 4 % (one A + one A^T at 256 x 256 x 128 x 512: 898 us staged and
+// 908; contractions at 96 x 96 x 320 x 512, 241 and 244; a step at 64 x 64 x 512, 115
+// and 120).  Rows of less than a tile are short runs of a slab with as many
 // spectrum bytes: staged, 202 x 202 x 37 x 256 (linear) took 640 instead of
 // 612 us.  With plain loads (above) staging pays for Gram products alone (a step
 // at 96 x 96 x 626, 384 us direct, 357 staged; 72 x 72 x 500, 168 and 157; A + A^T
@@ -428,6 +422,13 @@ constexpr long long kCacheBytes = 256LL << 20;
 constexpr int kXlRows = 192;
 constexpr size_t kMaxLds = 160 * 1024;  // of a CU
 
+// Workgroup = TW tiles x KP row shares of one (group, tile group, pair group).
+// Workgroups are dealt to the eight XCDs round-robin by index, so the units,
+// in group order, are cut into eight contiguous ranges, one per XCD, each taken
+// in order: the pair groups of a group, and the groups a large class is split
+// into (adjacent, reading the same slab), run on one XCD at about the same
+// time, and every read of a slab after the first comes from that XCD's L2
+// instead of HBM.
 template <typename HT, int V, int CT, int U, bool NT, bool WT, bool XL>
 __global__ __launch_bounds__(256, (CT > 1 ? 2 : 3)) void k_contract(ContractArgs a, int TW, int KP, int tgroups,
                                                                      int pgroups, int ntile) {
@@ -461,7 +462,10 @@ static pat_status launch_u(const ContractArgs& a, dim3 grid, int TW, int KP, int
   // writes into the slab stream costs more than their bytes (1.55 GB read in
   // 0.23 ms without stores, 0.29 with 135 MB of them), written through a
   // little less: Gram products (whole blocks) 157 against 160 us a step at
-  // 256 x 256 x 128.  A's spectra stay cached for the transform that follows.
+  // 256 x 256 x 128; one A + one A^T with A^T's lines written through and not:
+  // 128 x 128 x 256 x 256, 244 and 250 us, 64 x 64 x 512 x 512, 218 and 223.  A's
+  // spectra stay cached for the transform that follows (written through as
+  // well: 256 x 256 x 128 x 512, 902 and 901; 202 x 202 x 32 x 256 linear, 551 and 555).
   const bool wt = a.nj % 16 == 0 && (a.gram || a.ni >= 256);
   const dim3 block(64 * TW * KP);
   // the sums that waves of a workgroup pass on and, in the kernels that stage
@@ -476,7 +480,7 @@ static pat_status launch_u(const ContractArgs& a, dim3 grid, int TW, int KP, int
                 : nt     ? k_contract<HT, V, CT, U, true, false, false>
                 : wt     ? k_contract<HT, V, CT, U, false, true, false>
                          : k_contract<HT, V, CT, U, false, false, false>;
-  if constexpr (CT == 1 && V * sizeof(HT) == 16) {
+  if constexpr (CT == 1 && sizeof(HT) == 4) {
     if (xl)  // (rows of whole 16 values are whole 64 bytes: no written-through form with plain loads)
       kernel = !nt ? k_contract<HT, V, CT, U, false, false, true>
                : wt ? k_contract<HT, V, CT, U, true, true, true>
@@ -513,8 +517,13 @@ static pat_status launch_t(const ContractArgs& a, hipStream_t st) {
   if (nblk > 0x7fffffffLL) return fail(PAT_EUNSUPPORTED, "contraction grid too large");
   const dim3 grid((unsigned)nblk);
   const bool big = a.reuse_bytes > kCacheBytes, nt = big && (size_t)a.s_row * sizeof(HT) % 64 == 0;
-  const bool xl = CT == 1 && V * sizeof(HT) == 16 && (nt || (big && a.gram)) && a.members > 2 && a.ni >= kXlRows &&
+  const bool xl = CT == 1 && sizeof(HT) == 4 && (nt || (big && a.gram)) && a.members > 2 && a.ni >= kXlRows &&
                   a.nj >= 64 && (size_t)8 * xl_stride(a.ni) <= 64 * 1024;
+  // Row blocks per register buffer: four where a wave's blocks come in fours, so
+  // that no load is wasted, else two (one A + one A^T with two instead: 256 x 256 x
+  // 128 x 512, contractions 604 and 610 us; a step at 96 x 96 x 320, 121 and 124; on the
+  // other side 202 x 202 x 32 x 256 linear, 285 and 272; four at any length: A^T at
+  // 256 x 256 x 24 x 300, 55 and 62 us)
   const int share = (a.ni >> 3) / KP;  // row blocks of a wave
   constexpr int U4 = CT == 1 && V <= 4 ? 4 : 2;
   if (CT == 1 && V <= 4 && share % 4 == 0)

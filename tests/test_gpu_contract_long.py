@@ -20,8 +20,8 @@ CASES = [
     (256, 33, 419, "f32"),     # rows of 33 and 419 values: plain
     (144, 213, 211, "f32"),    # 864- and 848-byte rows: plain and long sums
     (144, 208, 195, "f32"),    # rows of 195 values: plain; A^T: staged, 832-byte rows, four tiles
-    (128, 213, 350, "bf16"),   # A: staged with scales, 704-byte rows, three tiles
-    (144, 93, 389, "bf16"),    # A^T: staged, one tile shared by four waves
+    (128, 213, 350, "bf16"),   # A: scales, 704-byte rows, three tiles
+    (144, 93, 389, "bf16"),    # A^T: 192-byte rows, one tile shared by four waves
     (128, 203, 389, "f16"),    # rows of 203 and 389 values: plain
 ]
 
