@@ -438,7 +438,7 @@ __global__ __launch_bounds__(256, (CT > 1 ? 2 : 3)) void k_contract(ContractArgs
   const int u = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (u >= units) return;  // whole workgroup: padding of the grid
   const int pg = u % pgroups, tg = (u / pgroups) % tgroups, t = u / (pgroups * tgroups);
-  const int4 grp = a.groups[t];  // first spectrum row, members, slab
+  const int4 grp = a.groups[t];  // first spectrum row, members, slab, whether other groups read it
   const int np = grp.y * a.B, pg0 = pg * 8 * CT;
   if (pg0 >= np) return;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -450,6 +450,15 @@ __global__ __launch_bounds__(256, (CT > 1 ? 2 : 3)) void k_contract(ContractArgs
   }
   if constexpr (CT == 2) {
     if (np - pg0 <= 8) return stream_tile<HT, V, 1, 2, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
+  }
+  // A slab that two or three groups read: non-temporal, most of its lines are gone
+  // before the next group asks for them.  A in float32 takes plain loads there
+  // (read at 256 x 256 x 128 x 512: 1.632 GB, now 1.588; one A + one A^T 904 us, now
+  // 901; 128 x 128 x 192 x 224, 191 and 186; 256 x 256 x 32 x 512, 436 and 438); A^T's
+  // result and 16-bit slabs, at twice the spectra per slab byte, lose as much in
+  // the transforms, whose lines the slabs then displace (906 and 914 us for A^T)
+  if constexpr (NT && !WT && CT == 1 && sizeof(HT) == 4) {
+    if (grp.w) return stream_tile<HT, V, CT, U, false, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
   }
   stream_tile<HT, V, CT, U, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
 }

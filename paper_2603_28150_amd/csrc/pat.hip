@@ -212,7 +212,7 @@ struct Classes {
   std::vector<int32_t> members;    // [nitem][G]
   std::vector<int32_t> kclass;     // [nk] slab of frequency k
   std::vector<int32_t> rowmap;     // [nk] spectrum row of frequency k
-  std::vector<int4> groups;        // members of a class by eights: first row, count, slab, 0
+  std::vector<int4> groups;        // members of a class by eights: first row, count, slab, whether there are more
   int n() const { return (int)freq.size() / 2; }
   int nitem() const { return (int)item_slab.size(); }
 };
@@ -270,7 +270,7 @@ static Classes make_classes(const pat_geometry& g) {
     // items are filled in order, so a class's rows are consecutive
     const int row0 = C.nitem() * C.G;
     for (int i0 = 0; i0 < (int)mem.size(); i0 += kGroup)
-      C.groups.push_back(make_int4(row0 + i0, std::min(kGroup, (int)mem.size() - i0), gi, 0));
+      C.groups.push_back(make_int4(row0 + i0, std::min(kGroup, (int)mem.size() - i0), gi, (int)mem.size() > kGroup));
     for (size_t i0 = 0; i0 < mem.size(); i0 += C.G) {
       const int item = (int)C.item_slab.size();
       C.item_slab.push_back(gi);

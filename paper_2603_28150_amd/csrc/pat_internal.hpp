@@ -74,7 +74,7 @@ pat_status fft2_c2r(const float2* X, float2* T, float* f, int fx, int fy, int nx
 // out[r][obj*nj + j] = sum_i slab_s[i][j] * in[r][obj*ni + i] (* scales) for
 // the member rows r of every group of frequencies and objects obj < B.  A
 // group is up to kGroup members of one class: groups[t] = (first spectrum
-// row, members, slab s, 0), its rows consecutive.
+// row, members, slab s, whether the class has other groups), its rows consecutive.
 constexpr int kGroup = 8;
 struct ContractArgs {
   const void* slab;          // [nslab][ni][s_row] of the storage type
