@@ -27,7 +27,7 @@
 // 128 x 512, 308 / 307, now 308 / 311 (5.6 TB/s of slabs and spectra); with bf16
 // slabs 186 / 204, now 182 / 181 (groups of 8 members read a slab once that two
 // items of 4 read twice).  contract() says which products go to the half-block
-// kernel (contract_sym.hip) and the vector units (contract_vec.hip) instead.
+// kernel (contract_sym.hip) and the vector units (contract_pair.hip) instead.
 #include <algorithm>
 #include <type_traits>
 
@@ -553,17 +553,14 @@ static pat_status launch_16(const ContractArgs& a, hipStream_t st) {
   return launch_t<HT, 8, 1>(a, st);
 }
 
-// Gram products that the vector units' kernel takes: of one object, from HBM, of
-// more than 128 rows that are not whole 128-byte lines.  With two members per
-// class it wins where the groups are many (a step, vector / matrix: 256 x 192 x
-// 140, 259 / 285 us; 96 x 64 x 400, 211 / 239; 48 x 32 x 1050, 344 / 394; of whole lines,
-// 256 x 192 x 192, 418 / 413; 153 groups: 32 x 16 x 1601, 374 / 326), with eight
-// between 176 and 512 rows (144 x 144 x 391, 345 / 360; 72 x 72 x 500, 145 / 157;
-// 128 x 128 x 250, 130 / 144; fewer rows: 384 x 384 x 150, 520 / 488; more: 96 x 96 x
-// 700, 453 / 420; few groups: 48 x 48 x 620, 120 / 119).
-static bool vec_gram(const ContractArgs& a) {
-  if (!a.gram || a.B != 1 || a.ni <= 128 || a.s_row % 32 == 0 || a.reuse_bytes <= kCacheBytes) return false;
-  return a.members <= 2 ? a.ngroup >= 200 : a.ngroup >= 500 && a.ni >= 176 && a.ni <= 512;
+// Gram products that the vector units' kernel takes: of one object with two
+// members per class, from HBM, of more than 128 rows that are not whole 128-byte
+// lines, where the groups are many (a step, vector / matrix: 256 x 192 x 140,
+// 254 / 287 us; 96 x 64 x 400, 207 / 236; 48 x 32 x 1050, 348 / 395; of whole lines, 256 x
+// 192 x 192, 418 / 411; 153 groups: 32 x 16 x 1601, 374 / 333).
+static bool pair_gram(const ContractArgs& a) {
+  return a.gram && a.B == 1 && a.members <= 2 && a.ni > 128 && a.s_row % 32 != 0 && a.reuse_bytes > kCacheBytes &&
+         a.ngroup >= 200;
 }
 
 pat_status contract(const ContractArgs& a, int hdtype, hipStream_t st) {
@@ -572,8 +569,7 @@ pat_status contract(const ContractArgs& a, int hdtype, hipStream_t st) {
       (long long)kGroup * a.out_rs > (1LL << 27))
     return fail(PAT_EUNSUPPORTED, "contraction slab or spectrum rows beyond 32-bit offsets");
   // one object on the two-member fold: the vector units' kernel
-  if (a.members <= 2 && a.B == 1 && !a.gram) return contract_vec(a, hdtype, st);
-  if (vec_gram(a)) return contract_vec(a, hdtype, st);
+  if ((a.members <= 2 && a.B == 1 && !a.gram) || pair_gram(a)) return contract_pair(a, hdtype, st);
   // Gram products from half of each block, where the units (a group's 8 pairs,
   // a wave each) fill the CUs and, for one object, rows start at whole 64-byte
   // pieces (a step of one object at 108 x 108 x 100, 400-byte rows: 42.0 us

@@ -1,20 +1,19 @@
-// The per-frequency contraction (step (ii) of Sec. 3.2) of one object on the
-// vector units.
+// The per-frequency contraction (step (ii) of Sec. 3.2) of one object on grids
+// that are not square, whose classes hold at most two frequencies (m, +-p).
 //
-// Where the matrix kernel (contract.hip) is not the better one: on grids that
-// are not square, whose classes hold at most two frequencies (m, +-p), it would
-// fill a quarter of its instructions, while the vector units do the same
-// products in the time the slab takes to arrive (one A + one A^T, float32,
-// vector and matrix: 192 x 32 transforms x 54 x 476, 118 and 126 us; 96 x 108 x 95 x
-// 167, 127 and 130; 192 x 96 x 50 x 301, 197 and 205); and in Gram products
-// beyond 128 depths whose rows are not whole 128-byte lines, since here a
-// workgroup reads whole rows and meets no line twice (a step at 256 x 192 x 200,
-// 461 and 488 us; 128 x 96 x 300, 251 and 278; 96 x 96 x 300, 110 and 122).
-//
-// A slab (or, for long rows, half of every row) belongs to one workgroup: lanes
-// of a row group cover one row with 16-byte non-temporal loads, row groups take
+// With two members a slab value meets four spectrum parts: the matrix kernel
+// (contract.hip) would fill a quarter of its instructions, while the vector
+// units do the same products in the time the slab takes to arrive.  A slab
+// (or, for long rows, half of every row) belongs to one workgroup: lanes of a
+// row group cover one row with 16-byte non-temporal loads, row groups take
 // interleaved rows, the member spectra sit in LDS, and an LDS tree adds the
-// row groups' sums in a fixed order.
+// row groups' sums in a fixed order.  Sums of 16 rows are kept apart before they
+// join the total, as in the matrix kernel: the loads hide it (a step at 256 x 192 x
+// 140, 256 us without, 254 with).  Measured against the matrix kernel on this
+// fold (one A + one A^T, float32): 192 x 32 transforms x 54 x 476, 118 and 126 us;
+// 96 x 108 x 95 x 167, 127 and 130 us; 192 x 96 x 50 x 301, 197 and 205 us.  Gram
+// products beyond 128 depths come here where contract() says so: a workgroup
+// reads whole rows, so that rows of broken lines meet no line twice.
 #include <algorithm>
 #include <type_traits>
 
@@ -27,16 +26,30 @@ namespace pat {
 constexpr int kRowParts = 2;  // workgroups per slab for long rows
 template <typename HT> constexpr int kRows = std::is_same<HT, float>::value ? 2 : 4;  // rows per register buffer
 
-// One slab (or part of its rows) with GG member slots, of which grp.y are
-// filled.  Uniform per workgroup.
-template <typename HT, int GG>
-__device__ __forceinline__ void vec_group(const ContractArgs& a, int lr_log2, int4 grp, int j0, int njl,
-                                          float4* smem_raw) {
+// float32: two rows per register buffer instead of four, so that the kernel
+// fits 128 registers and four waves per SIMD (measured faster on short rows,
+// neutral on long ones)
+template <typename HT>
+__global__ __launch_bounds__(256, (std::is_same<HT, float>::value ? 4 : 1)) void k_contract_pair(ContractArgs a,
+                                                                                                int lr_log2, int JS,
+                                                                                                int chpart) {
+  extern __shared__ float4 smem_raw[];
+  // workgroups are dealt to the eight XCDs round-robin by index: the units
+  // (class, row part) are cut into eight contiguous ranges, one per XCD
+  const int units = a.ngroup * JS;
+  const int per_xcd = (units + 7) >> 3;
+  const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (unit >= units) return;  // whole workgroup: padding of the grid
+  const int t = unit / JS, part = unit - t * JS;
+  const int4 grp = a.groups[t];  // first spectrum row, members (1 or 2), slab
+  constexpr int GG = 2;
   typedef Slab<HT> SL;
   typedef typename SL::raw_t raw_t;
   constexpr int VEC = SL::VEC;
   constexpr int U = kRows<HT>;      // rows per register buffer
   constexpr int NS = VEC * GG * 2;  // accumulators per thread
+  const int j0 = part * chpart * VEC;
+  const int njl = min(a.nj - j0, chpart * VEC);
   float2* xin = reinterpret_cast<float2*>(smem_raw);
   float* red = reinterpret_cast<float*>(smem_raw);
   const int tid = threadIdx.x;
@@ -114,9 +127,16 @@ __device__ __forceinline__ void vec_group(const ContractArgs& a, int lr_log2, in
   }
   __syncthreads();
 
-  float acc[NS];
+  float acc[NS], sum16[NS];
 #pragma unroll
-  for (int s = 0; s < NS; ++s) acc[s] = 0.f;
+  for (int s = 0; s < NS; ++s) acc[s] = sum16[s] = 0.f;
+  auto flush = [&]() {
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      acc[s] += sum16[s];
+      sum16[s] = 0.f;
+    }
+  };
 
   auto fma_rows = [&](const raw_t (&raw)[U], int i0) {
 #pragma unroll
@@ -131,20 +151,26 @@ __device__ __forceinline__ void vec_group(const ContractArgs& a, int lr_log2, in
         const float h = SL::get(raw[u], v);
 #pragma unroll
         for (int g = 0; g < GG; ++g) {
-          float* p = &acc[(v * GG + g) * 2];
+          float* p = &sum16[(v * GG + g) * 2];
           p[0] = fmaf(h, xv[g].x, p[0]);
           p[1] = fmaf(h, xv[g].y, p[1]);
         }
       }
     }
   };
+  int left = 16;  // rows to the next addition to the total
   for (int i0 = rg; i0 < a.ni; i0 += 2 * R * U) {
     load_rows(rb, i0 + R * U);
     fma_rows(ra, i0);
     if (i0 + R * U >= a.ni) break;
     load_rows(ra, i0 + 2 * R * U);
     fma_rows(rb, i0 + R * U);
+    if ((left -= 2 * U) <= 0) {
+      flush();
+      left = 16;
+    }
   }
+  flush();
 
   // add the partial sums of the R row groups (fixed order: deterministic)
   for (int half = R >> 1; half >= 1; half >>= 1) {
@@ -244,32 +270,8 @@ __device__ __forceinline__ void vec_group(const ContractArgs& a, int lr_log2, in
   }
 }
 
-// float32: two rows per register buffer instead of four, so that the kernel
-// fits 128 registers and four waves per SIMD (measured faster on short rows,
-// neutral on long ones)
-template <typename HT, int G>
-__global__ __launch_bounds__(256, (std::is_same<HT, float>::value ? 4 : 1)) void k_contract_vec(ContractArgs a,
-                                                                                               int lr_log2, int JS,
-                                                                                               int chpart) {
-  extern __shared__ float4 smem_raw[];
-  // workgroups are dealt to the eight XCDs round-robin by index: the units
-  // (group, row part) are cut into eight contiguous ranges, one per XCD
-  const int units = a.ngroup * JS;
-  const int per_xcd = (units + 7) >> 3;
-  const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (unit >= units) return;  // whole workgroup: padding of the grid
-  const int t = unit / JS, part = unit - t * JS;
-  const int4 grp = a.groups[t];  // first spectrum row, members, slab
-  constexpr int VEC = Slab<HT>::VEC;
-  const int j0 = part * chpart * VEC, njl = min(a.nj - j0, chpart * VEC);
-  if constexpr (G == 8) {
-    if (grp.y <= 4) return vec_group<HT, 4>(a, lr_log2, grp, j0, njl, smem_raw);  // the cheaper body
-  }
-  vec_group<HT, G>(a, lr_log2, grp, j0, njl, smem_raw);
-}
-
-template <typename HT, int G>
-static pat_status launch_vec(const ContractArgs& a, hipStream_t st) {
+template <typename HT>
+static pat_status launch_pair(const ContractArgs& a, hipStream_t st) {
   constexpr int VEC = Slab<HT>::VEC;
   // rows of 128 or more 16-byte chunks are split over kRowParts workgroups
   // per slab (halves of 1 KB and more still stream well; shorter parts
@@ -281,23 +283,23 @@ static pat_status launch_vec(const ContractArgs& a, hipStream_t st) {
   int lr_log2 = 0;
   while ((1 << lr_log2) < chpart) ++lr_log2;
   const int Lr = 1 << lr_log2, R = 256 / Lr;
-  const size_t red_bytes = R > 1 ? (size_t)(R / 2) * Lr * VEC * G * 2 * sizeof(float) : 0;
-  const size_t in_bytes = (size_t)a.ni * G * sizeof(float2);
-  const size_t out_bytes = (size_t)chpart * VEC * G * sizeof(float2);
+  const size_t red_bytes = R > 1 ? (size_t)(R / 2) * Lr * VEC * 4 * sizeof(float) : 0;
+  const size_t in_bytes = (size_t)a.ni * 2 * sizeof(float2);
+  const size_t out_bytes = (size_t)chpart * VEC * 2 * sizeof(float2);
   const size_t lds = std::max(red_bytes, std::max(in_bytes, out_bytes));
   if (lds > 160 * 1024) return fail(PAT_EUNSUPPORTED, "contraction input vector does not fit in LDS");
   const long long nblk = ((long long)a.ngroup * JS + 7) / 8 * 8;
   if (nblk > 0x7fffffffLL) return fail(PAT_EUNSUPPORTED, "contraction grid too large");
-  k_contract_vec<HT, G><<<dim3((unsigned)nblk), 256, lds, st>>>(a, lr_log2, JS, chpart);
-  PAT_LAUNCHED("contraction (vector units)");
+  k_contract_pair<HT><<<dim3((unsigned)nblk), 256, lds, st>>>(a, lr_log2, JS, chpart);
+  PAT_LAUNCHED("contraction (two members)");
   return PAT_OK;
 }
 
-pat_status contract_vec(const ContractArgs& a, int hdtype, hipStream_t st) {
-  if (a.B != 1) return fail(PAT_EINVAL, "the vector contraction takes one object");
-  if (hdtype == PAT_H_F32) return a.members > 2 ? launch_vec<float, 8>(a, st) : launch_vec<float, 2>(a, st);
-  if (a.members > 2 || a.out_sub) return fail(PAT_EINVAL, "the vector contraction of 16-bit slabs: two members");
-  return hdtype == PAT_H_BF16 ? launch_vec<bf16_t, 2>(a, st) : launch_vec<f16_t, 2>(a, st);
+pat_status contract_pair(const ContractArgs& a, int hdtype, hipStream_t st) {
+  if (a.members > 2 || a.B != 1) return fail(PAT_EINVAL, "the two-member contraction takes one object");
+  if (hdtype == PAT_H_F32) return launch_pair<float>(a, st);
+  if (hdtype == PAT_H_BF16) return launch_pair<bf16_t>(a, st);
+  return launch_pair<f16_t>(a, st);
 }
 
 }  // namespace pat

@@ -92,8 +92,8 @@ struct ContractArgs {
   long long reuse_bytes;   // library bytes a caller's loop reads before it comes back to this launch's slabs
 };
 pat_status contract(const ContractArgs& a, int hdtype, hipStream_t st);
-// the same for B = 1 on the vector units (16-bit slabs: groups of at most two members, no out_sub)
-pat_status contract_vec(const ContractArgs& a, int hdtype, hipStream_t st);
+// the same for B = 1 and groups of at most two members, on the vector units
+pat_status contract_pair(const ContractArgs& a, int hdtype, hipStream_t st);
 // the same for symmetric float32 slabs of at most 128 rows, reading half of each (nt: non-temporal loads)
 pat_status contract_sym(const ContractArgs& a, bool nt, hipStream_t st);
 

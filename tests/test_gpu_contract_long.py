@@ -15,14 +15,16 @@ pytestmark = pytest.mark.gpu
 
 #        n  nz  nt  library    (both row lengths and summed lengths in turn)
 CASES = [
-    (192, 77, 229, "f32"),     # A^T: staged, 320-byte rows, two tiles; A: 928-byte rows, plain
+    (192, 77, 229, "f32"),     # A^T: staged, 320-byte rows, two tiles
     (192, 80, 337, "f32"),     # A^T: staged, whole 64-byte rows and stores
-    (256, 33, 419, "f32"),     # rows of 33 and 419 values: plain
-    (144, 213, 211, "f32"),    # 864- and 848-byte rows: plain and long sums
+    (256, 33, 419, "f32"),     # broken rows, short sums
+    (144, 213, 211, "f32"),    # 864- and 848-byte rows: plain, staged
     (144, 208, 195, "f32"),    # rows of 195 values: plain; A^T: staged, 832-byte rows, four tiles
+    (128, 131, 300, "f32"),    # plain, A direct and A^T staged
+    (128, 66, 777, "f32"),     # A^T: plain, staged, two tiles of which the second has two outputs
     (128, 213, 350, "bf16"),   # A: scales, 704-byte rows, three tiles
     (144, 93, 389, "bf16"),    # A^T: 192-byte rows, one tile shared by four waves
-    (128, 203, 389, "f16"),    # rows of 203 and 389 values: plain
+    (128, 203, 389, "f16"),    # broken rows
 ]
 
 

@@ -41,9 +41,9 @@ def test_many_rows(nx, ny, nz, B):
 
 @pytest.mark.parametrize("nx,ny,nz", [(72, 72, 373), (72, 72, 374), (128, 128, 217), (96, 64, 262), (48, 32, 1030), (64, 32, 777)])
 def test_broken_lines(nx, ny, nz):
-    # blocks whose rows are not whole 128-byte lines: one object on the vector
-    # units, with classes of eight and of two members, odd and even rows, rows
-    # over one and two workgroups, with and without the subtracted spectrum
+    # blocks whose rows are not whole 128-byte lines: one object, classes of
+    # eight members and (on the vector units) of two, odd and even rows, rows over
+    # one and two workgroups, with and without the subtracted spectrum
     op = Operator(Geometry.paper_like(nx, ny, nz, 6))
     i = op.info()
     assert i["gram_bytes"] > 256 << 20
