@@ -398,12 +398,16 @@ __device__ __forceinline__ void stream_tile(const ContractArgs& a, int row0, int
 // and non-temporal loads stream faster (7.1 against 6.2 TB/s on a plain read
 // of 1.55 GB).  One A + one A^T: 128 x 128 x 64 x 256 (210 MB in both layouts)
 // 108 us plain, 111 non-temporal; 128 x 128 x 96 x 384 (470 MB) 187 and 174.
-// Rows that do not start at whole 64-byte pieces take plain loads at any size:
-// neighbouring tiles share a line there, and a line loaded as non-temporal
-// is often gone from the L2 when the second tile asks for it (1.2 times the
-// slab's bytes fetched at 600 values per row, 1.0 plain).  One A + one A^T,
-// non-temporal and plain: 128 x 128 x 130 x 402, 180 and 157 us; 128 x 128 x 99 x
-// 997, 314 and 258; 202 x 202 x 37 x 256 (linear) 332 and 324.
+// Long float32 products of rows that do not start at whole 64-byte pieces take
+// plain loads at any size: neighbouring tiles share a line there, and a line
+// loaded as non-temporal is often gone from the L2 when the second tile asks for
+// it (1.2 times the slab's bytes fetched at 600 values per row, 1.0 plain).  One A +
+// one A^T (medians over ten placements in memory), non-temporal and plain: 128 x
+// 128 x 130 x 402, 258 and 247 us; 144 x 144 x 200 x 200, 240 and 231; 128 x 128 x 67 x
+// 1643, 571 and 526; short sums and short rows lose, as the plain loads push the
+// spectra out of that cache: 128 x 128 x 33 x 700, 187 and 192; 192 x 192 x 100 x 229,
+// 260 and 264 with A^T plain; 384 x 384 x 100 x 101, 512 and 522.  16-bit slabs, half as
+// long, lose throughout (144 x 144 x 217 x 333, 254 and 266).
 constexpr long long kCacheBytes = 256LL << 20;
 
 // Rows from which the spectra are staged in LDS (XL; float32 slabs: with 16-bit
@@ -415,10 +419,7 @@ constexpr long long kCacheBytes = 256LL << 20;
 // 908; contractions at 96 x 96 x 320 x 512, 241 and 244; a step at 64 x 64 x 512, 115
 // and 120).  Rows of less than a tile are short runs of a slab with as many
 // spectrum bytes: staged, 202 x 202 x 37 x 256 (linear) took 640 instead of
-// 612 us.  With plain loads (above) staging pays for Gram products alone (a step
-// at 96 x 96 x 626, 384 us direct, 357 staged; 72 x 72 x 500, 168 and 157; A + A^T
-// at 96 x 96 x 131 x 517, 119 direct and 126 staged; 128 x 128 x 99 x 997, 258 and
-// 276).
+// 612 us.
 constexpr int kXlRows = 192;
 constexpr size_t kMaxLds = 160 * 1024;  // of a CU
 
@@ -525,9 +526,11 @@ static pat_status launch_t(const ContractArgs& a, hipStream_t st) {
   const long long nblk = ((long long)a.ngroup * tgroups * pgroups + 7) / 8 * 8;
   if (nblk > 0x7fffffffLL) return fail(PAT_EUNSUPPORTED, "contraction grid too large");
   const dim3 grid((unsigned)nblk);
-  const bool big = a.reuse_bytes > kCacheBytes, nt = big && (size_t)a.s_row * sizeof(HT) % 64 == 0;
-  const bool xl = CT == 1 && sizeof(HT) == 4 && (nt || (big && a.gram)) && a.members > 2 && a.ni >= kXlRows &&
-                  a.nj >= 64 && (size_t)8 * xl_stride(a.ni) <= 64 * 1024;
+  const bool big = a.reuse_bytes > kCacheBytes;
+  const bool broken = sizeof(HT) == 4 && a.s_row % 16 != 0 && a.ni >= 128 && (a.nj >= 128 || (a.nj > tn && a.ni >= 256));
+  const bool nt = big && !broken;
+  const bool xl = CT == 1 && sizeof(HT) == 4 && big && a.members > 2 && a.ni >= kXlRows && a.nj >= 64 &&
+                  (size_t)8 * xl_stride(a.ni) <= 64 * 1024;
   // Row blocks per register buffer: four where a wave's blocks come in fours, so
   // that no load is wasted, else two (one A + one A^T with two instead: 256 x 256 x
   // 128 x 512, contractions 604 and 610 us; a step at 96 x 96 x 320, 121 and 124; on the
