@@ -431,7 +431,7 @@ constexpr size_t kMaxLds = 160 * 1024;  // of a CU
 // time, and every read of a slab after the first comes from that XCD's L2
 // instead of HBM.
 template <typename HT, int V, int CT, int U, bool NT, bool WT, bool XL>
-__global__ __launch_bounds__(256, (CT > 1 ? 2 : 3)) void k_contract(ContractArgs a, int TW, int KP, int tgroups,
+__global__ __launch_bounds__(512, (CT > 1 ? 2 : 3)) void k_contract(ContractArgs a, int TW, int KP, int tgroups,
                                                                      int pgroups, int ntile) {
   extern __shared__ float red[];
   const int units = a.ngroup * tgroups * pgroups;
@@ -459,7 +459,7 @@ __global__ __launch_bounds__(256, (CT > 1 ? 2 : 3)) void k_contract(ContractArgs
   // result and 16-bit slabs, at twice the spectra per slab byte, lose as much in
   // the transforms, whose lines the slabs then displace (906 and 914 us for A^T)
   if constexpr (NT && !WT && CT == 1 && sizeof(HT) == 4) {
-    if (grp.w) return stream_tile<HT, V, CT, U, false, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
+    if (grp.w && !a.gram) return stream_tile<HT, V, CT, U, false, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
   }
   stream_tile<HT, V, CT, U, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
 }
@@ -523,14 +523,23 @@ static pat_status launch_t(const ContractArgs& a, hipStream_t st) {
     TW = 1;
     tgroups = ntile;
   }
-  const long long nblk = ((long long)a.ngroup * tgroups * pgroups + 7) / 8 * 8;
-  if (nblk > 0x7fffffffLL) return fail(PAT_EUNSUPPORTED, "contraction grid too large");
-  const dim3 grid((unsigned)nblk);
   const bool big = a.reuse_bytes > kCacheBytes;
   const bool broken = sizeof(HT) == 4 && a.s_row % 16 != 0 && a.ni >= 128 && (a.nj >= 128 || (a.nj > tn && a.ni >= 256));
   const bool nt = big && !broken;
   const bool xl = CT == 1 && sizeof(HT) == 4 && big && a.members > 2 && a.ni >= kXlRows && a.nj >= 64 &&
                   (size_t)8 * xl_stride(a.ni) <= 64 * 1024;
+  // Staged products of more than four tiles: up to eight of them share one
+  // staging and read whole rows, where the groups are one and a half per CU or more
+  // (a step at 96 x 96 x 400, 185 us and 171 so; one A + one A^T at 96 x 96 x 320 x 512,
+  // 310 and 298; 64 x 64 x 512 x 512, 215 and 206; of 275 groups, 48 x 48 x 768, 146 and
+  // 158; rows of broken pieces no better: 72 x 72 x 500, 164 and 172)
+  if (xl && nt && KP == 1 && ntile > 4 && a.ngroup >= 384) {
+    tgroups = (ntile + 7) / 8;
+    TW = (ntile + tgroups - 1) / tgroups;
+  }
+  const long long nblk = ((long long)a.ngroup * tgroups * pgroups + 7) / 8 * 8;
+  if (nblk > 0x7fffffffLL) return fail(PAT_EUNSUPPORTED, "contraction grid too large");
+  const dim3 grid((unsigned)nblk);
   // Row blocks per register buffer: four where a wave's blocks come in fours, so
   // that no load is wasted, else two (one A + one A^T with two instead: 256 x 256 x
   // 128 x 512, contractions 604 and 610 us; a step at 96 x 96 x 320, 121 and 124; on the

@@ -20,6 +20,8 @@ CASES = [
     (256, 33, 419, "f32"),     # broken rows, short sums
     (144, 213, 211, "f32"),    # 864- and 848-byte rows: plain, staged
     (144, 208, 195, "f32"),    # rows of 195 values: plain; A^T: staged, 832-byte rows, four tiles
+    (96, 208, 334, "f32"),     # A: six tiles in one workgroup; A^T: four
+    (96, 333, 784, "f32"),     # A^T: six tiles of broken rows; A: thirteen in two workgroups
     (128, 131, 300, "f32"),    # plain, A direct and A^T staged
     (128, 66, 777, "f32"),     # A^T: plain, staged, two tiles of which the second has two outputs
     (128, 213, 350, "bf16"),   # A: scales, 704-byte rows, three tiles
