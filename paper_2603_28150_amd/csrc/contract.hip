@@ -430,10 +430,20 @@ constexpr size_t kMaxLds = 160 * 1024;  // of a CU
 // into (adjacent, reading the same slab), run on one XCD at about the same
 // time, and every read of a slab after the first comes from that XCD's L2
 // instead of HBM.
-template <typename HT, int V, int CT, int U, bool NT, bool WT, bool XL>
-__global__ __launch_bounds__(512, (CT > 1 ? 2 : 3)) void k_contract(ContractArgs a, int TW, int KP, int tgroups,
+//
+// LD: how slabs are loaded.  A slab that two or three groups read: non-temporal,
+// most of its lines are gone before the next group asks for them.  A in float32
+// takes plain loads there, kStreamOnce (read at 256 x 256 x 128 x 512: 1.632 GB, now
+// 1.588; one A + one A^T 904 us, now 901; 128 x 128 x 192 x 224, 191 and 186).  Short
+// sums, A^T's result and 16-bit slabs, at more spectra per slab byte, lose as
+// much in the transforms, whose lines the slabs then displace (256 x 256 x 32 x
+// 512, 436 and 438; A^T, 906 and 914; 202 x 202 x 37 x 256 linear, A^T 179 and 180).
+enum Loads { kPlain, kStream, kStreamOnce };
+template <typename HT, int V, int CT, int U, int LD, bool WT, bool XL>
+__global__ __launch_bounds__((XL ? 512 : 256), (CT > 1 ? 2 : 3)) void k_contract(ContractArgs a, int TW, int KP, int tgroups,
                                                                      int pgroups, int ntile) {
   extern __shared__ float red[];
+  constexpr bool NT = LD != kPlain;
   const int units = a.ngroup * tgroups * pgroups;
   const int per_xcd = (units + 7) >> 3;
   const int u = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
@@ -452,14 +462,8 @@ __global__ __launch_bounds__(512, (CT > 1 ? 2 : 3)) void k_contract(ContractArgs
   if constexpr (CT == 2) {
     if (np - pg0 <= 8) return stream_tile<HT, V, 1, 2, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
   }
-  // A slab that two or three groups read: non-temporal, most of its lines are gone
-  // before the next group asks for them.  A in float32 takes plain loads there
-  // (read at 256 x 256 x 128 x 512: 1.632 GB, now 1.588; one A + one A^T 904 us, now
-  // 901; 128 x 128 x 192 x 224, 191 and 186; 256 x 256 x 32 x 512, 436 and 438); A^T's
-  // result and 16-bit slabs, at twice the spectra per slab byte, lose as much in
-  // the transforms, whose lines the slabs then displace (906 and 914 us for A^T)
-  if constexpr (NT && !WT && CT == 1 && sizeof(HT) == 4) {
-    if (grp.w && !a.gram) return stream_tile<HT, V, CT, U, false, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
+  if constexpr (LD == kStreamOnce) {
+    if (grp.w) return stream_tile<HT, V, CT, U, false, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
   }
   stream_tile<HT, V, CT, U, NT, WT, XL>(a, grp.x, grp.z, tile, kpart, KP, pg0, np, red);
 }
@@ -486,15 +490,19 @@ static pat_status launch_u(const ContractArgs& a, dim3 grid, int TW, int KP, int
   const size_t lds = std::max((size_t)TW * KP * (KP > 1 ? CT : 1) * V * 256 * sizeof(float),
                               xl ? (size_t)8 * xl_stride(a.ni) : 0);
   if (lds > kMaxLds) return fail(PAT_EUNSUPPORTED, "contraction: sums and spectra do not fit in LDS");
-  auto kernel = nt && wt ? k_contract<HT, V, CT, U, true, true, false>
-                : nt     ? k_contract<HT, V, CT, U, true, false, false>
-                : wt     ? k_contract<HT, V, CT, U, false, true, false>
-                         : k_contract<HT, V, CT, U, false, false, false>;
+  auto kernel = nt && wt ? k_contract<HT, V, CT, U, kStream, true, false>
+                : nt     ? k_contract<HT, V, CT, U, kStream, false, false>
+                : wt     ? k_contract<HT, V, CT, U, kPlain, true, false>
+                         : k_contract<HT, V, CT, U, kPlain, false, false>;
   if constexpr (CT == 1 && sizeof(HT) == 4) {
+    const bool once = nt && !wt && !a.gram && a.ni > 64 && a.nj >= a.ni;
     if (xl)  // (rows of whole 16 values are whole 64 bytes: no written-through form with plain loads)
-      kernel = !nt ? k_contract<HT, V, CT, U, false, false, true>
-               : wt ? k_contract<HT, V, CT, U, true, true, true>
-                    : k_contract<HT, V, CT, U, true, false, true>;
+      kernel = !nt    ? k_contract<HT, V, CT, U, kPlain, false, true>
+               : wt   ? k_contract<HT, V, CT, U, kStream, true, true>
+               : once ? k_contract<HT, V, CT, U, kStreamOnce, false, true>
+                      : k_contract<HT, V, CT, U, kStream, false, true>;
+    else if (once)
+      kernel = k_contract<HT, V, CT, U, kStreamOnce, false, false>;
   }
   kernel<<<grid, block, lds, st>>>(a, TW, KP, tgroups, pgroups, ntile);
   PAT_LAUNCHED("contraction");

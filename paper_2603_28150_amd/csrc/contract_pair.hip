@@ -7,13 +7,16 @@
 // (or, for long rows, half of every row) belongs to one workgroup: lanes of a
 // row group cover one row with 16-byte non-temporal loads, row groups take
 // interleaved rows, the member spectra sit in LDS, and an LDS tree adds the
-// row groups' sums in a fixed order.  Sums of 16 rows are kept apart before they
-// join the total, as in the matrix kernel: the loads hide it (a step at 256 x 192 x
-// 140, 256 us without, 254 with).  Measured against the matrix kernel on this
+// row groups' sums in a fixed order.  Measured against the matrix kernel on this
 // fold (one A + one A^T, float32): 192 x 32 transforms x 54 x 476, 118 and 126 us;
-// 96 x 108 x 95 x 167, 127 and 130 us; 192 x 96 x 50 x 301, 197 and 205 us.  Gram
-// products beyond 128 depths come here where contract() says so: a workgroup
-// reads whole rows, so that rows of broken lines meet no line twice.
+// 96 x 108 x 95 x 167, 127 and 130 us; 192 x 96 x 50 x 301, 197 and 205 us.
+//
+// Gram products beyond 128 depths come here where contract() says so: a workgroup
+// reads whole rows, so that rows of broken lines meet no line twice.  Their
+// sums of 16 rows are kept apart before they join the total, as in the matrix
+// kernel, whose error they would otherwise pass (700 rows: 4.6e-7, 1.4e-7 so); the
+// loads of the long rows hide it (a step at 256 x 192 x 140, 256 us without, 254
+// with), those of short ones do not (144 x 192 x 21 x 162, bf16: 162 and 166).
 #include <algorithm>
 #include <type_traits>
 
@@ -29,7 +32,7 @@ template <typename HT> constexpr int kRows = std::is_same<HT, float>::value ? 2 
 // float32: two rows per register buffer instead of four, so that the kernel
 // fits 128 registers and four waves per SIMD (measured faster on short rows,
 // neutral on long ones)
-template <typename HT>
+template <typename HT, bool GRAM>
 __global__ __launch_bounds__(256, (std::is_same<HT, float>::value ? 4 : 1)) void k_contract_pair(ContractArgs a,
                                                                                                 int lr_log2, int JS,
                                                                                                 int chpart) {
@@ -127,16 +130,20 @@ __global__ __launch_bounds__(256, (std::is_same<HT, float>::value ? 4 : 1)) void
   }
   __syncthreads();
 
-  float acc[NS], sum16[NS];
+  float acc[NS], sum16[GRAM ? NS : 1];
 #pragma unroll
-  for (int s = 0; s < NS; ++s) acc[s] = sum16[s] = 0.f;
+  for (int s = 0; s < NS; ++s) acc[s] = 0.f;
   auto flush = [&]() {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
+    for (int s = 0; s < (GRAM ? NS : 0); ++s) {
       acc[s] += sum16[s];
       sum16[s] = 0.f;
     }
   };
+  if constexpr (GRAM) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s) sum16[s] = 0.f;
+  }
 
   auto fma_rows = [&](const raw_t (&raw)[U], int i0) {
 #pragma unroll
@@ -151,7 +158,7 @@ __global__ __launch_bounds__(256, (std::is_same<HT, float>::value ? 4 : 1)) void
         const float h = SL::get(raw[u], v);
 #pragma unroll
         for (int g = 0; g < GG; ++g) {
-          float* p = &sum16[(v * GG + g) * 2];
+          float* p = GRAM ? &sum16[(v * GG + g) * 2] : &acc[(v * GG + g) * 2];
           p[0] = fmaf(h, xv[g].x, p[0]);
           p[1] = fmaf(h, xv[g].y, p[1]);
         }
@@ -165,7 +172,7 @@ __global__ __launch_bounds__(256, (std::is_same<HT, float>::value ? 4 : 1)) void
     if (i0 + R * U >= a.ni) break;
     load_rows(ra, i0 + 2 * R * U);
     fma_rows(rb, i0 + R * U);
-    if ((left -= 2 * U) <= 0) {
+    if (GRAM && (left -= 2 * U) <= 0) {
       flush();
       left = 16;
     }
@@ -235,42 +242,27 @@ __global__ __launch_bounds__(256, (std::is_same<HT, float>::value ? 4 : 1)) void
   const size_t o0 = (size_t)grp.x * a.out_rs + j0;
   if ((njl & 1) == 0 && (a.nj & 1) == 0) {
     // two complex values (16 bytes) per store, non-temporal: the rows are
-    // not read again by this kernel.  kOut per thread: their values (and the
-    // subtracted ones) are all read before the first store; a load issued
-    // after a store would wait for it on the in-order memory counter
-    constexpr int kOut = 2;
+    // not read again by this kernel
     const int h = njl >> 1;
-    for (int e0 = tid; e0 < grp.y * h; e0 += 256 * kOut) {
-      v4f d[kOut], sub[kOut];
-      size_t o[kOut];
-#pragma unroll
-      for (int q = 0; q < kOut; ++q) {
-        const int e = min(e0 + q * 256, grp.y * h - 1), g = e / h, j = 2 * (e - g * h);
-        o[q] = o0 + (size_t)g * a.out_rs + j;
-        d[q] = *reinterpret_cast<const v4f*>(ob + g * njl + j);
-        sub[q] = a.out_sub ? *reinterpret_cast<const v4f*>(a.out_sub + o[q]) : v4f(0.f);
-      }
-      // differences on straight-line code (the empty asm keeps them out of
-      // the conditional stores, where each store would wait again)
-#pragma unroll
-      for (int q = 0; q < kOut; ++q) {
-        d[q] -= sub[q];
-        asm volatile("" : "+v"(d[q]));
-      }
-#pragma unroll
-      for (int q = 0; q < kOut; ++q)
-        if (e0 + q * 256 < grp.y * h) __builtin_nontemporal_store(d[q], reinterpret_cast<v4f*>(a.out + o[q]));
+    for (int e = tid; e < GG * h; e += 256) {
+      const int g = e >= h, j = 2 * (e - g * h);
+      if (g >= grp.y) continue;
+      v4f d = *reinterpret_cast<const v4f*>(ob + g * njl + j);
+      const size_t o = o0 + (size_t)g * a.out_rs + j;
+      if (GRAM && a.out_sub) d -= *reinterpret_cast<const v4f*>(a.out_sub + o);
+      __builtin_nontemporal_store(d, reinterpret_cast<v4f*>(a.out + o));
     }
   } else {
-    for (int e = tid; e < grp.y * njl; e += 256) {
-      const int g = e / njl;
-      const size_t o = o0 + (size_t)g * a.out_rs + (e - g * njl);
-      a.out[o] = a.out_sub ? csub(ob[e], a.out_sub[o]) : ob[e];
+    for (int e = tid; e < GG * njl; e += 256) {
+      const int g = e >= njl, j = e - g * njl;
+      if (g >= grp.y) continue;
+      const size_t o = o0 + (size_t)g * a.out_rs + j;
+      a.out[o] = GRAM && a.out_sub ? csub(ob[e], a.out_sub[o]) : ob[e];
     }
   }
 }
 
-template <typename HT>
+template <typename HT, bool GRAM>
 static pat_status launch_pair(const ContractArgs& a, hipStream_t st) {
   constexpr int VEC = Slab<HT>::VEC;
   // rows of 128 or more 16-byte chunks are split over kRowParts workgroups
@@ -290,16 +282,17 @@ static pat_status launch_pair(const ContractArgs& a, hipStream_t st) {
   if (lds > 160 * 1024) return fail(PAT_EUNSUPPORTED, "contraction input vector does not fit in LDS");
   const long long nblk = ((long long)a.ngroup * JS + 7) / 8 * 8;
   if (nblk > 0x7fffffffLL) return fail(PAT_EUNSUPPORTED, "contraction grid too large");
-  k_contract_pair<HT><<<dim3((unsigned)nblk), 256, lds, st>>>(a, lr_log2, JS, chpart);
+  k_contract_pair<HT, GRAM><<<dim3((unsigned)nblk), 256, lds, st>>>(a, lr_log2, JS, chpart);
   PAT_LAUNCHED("contraction (two members)");
   return PAT_OK;
 }
 
 pat_status contract_pair(const ContractArgs& a, int hdtype, hipStream_t st) {
   if (a.members > 2 || a.B != 1) return fail(PAT_EINVAL, "the two-member contraction takes one object");
-  if (hdtype == PAT_H_F32) return launch_pair<float>(a, st);
-  if (hdtype == PAT_H_BF16) return launch_pair<bf16_t>(a, st);
-  return launch_pair<f16_t>(a, st);
+  if (a.gram) return launch_pair<float, true>(a, st);
+  if (hdtype == PAT_H_F32) return launch_pair<float, false>(a, st);
+  if (hdtype == PAT_H_BF16) return launch_pair<bf16_t, false>(a, st);
+  return launch_pair<f16_t, false>(a, st);
 }
 
 }  // namespace pat

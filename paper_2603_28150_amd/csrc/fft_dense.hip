@@ -105,7 +105,8 @@ __device__ __forceinline__ void dense_tiles(const float2* tab, int N, int K4, in
 // slices per workgroup, or (PACK) 2^(5 - lsp) rows of 2^lsp slices
 template <int NT, bool PACK>
 __global__ __launch_bounds__(256) void k_dense_rows_r2c(const float* __restrict__ f, float2* __restrict__ T, int ny,
-                                                        int N, int S, int rs, int lsp, const float2* __restrict__ tw) {
+                                                        int N, int S, int rs, int lsp, int parts,
+                                                        const float2* __restrict__ tw) {
   extern __shared__ float2 dlds[];
   const int K = N / 2 + 1, K4 = dense_k4(N);
   float2* tab = dlds;
@@ -137,7 +138,7 @@ __global__ __launch_bounds__(256) void k_dense_rows_r2c(const float* __restrict_
   }
   __syncthreads();
   const int c = lane >> 4, l16 = lane & 15, s = s0 + (l16 & sm), ja = j0 + (l16 >> ls), jb = j0 + ((l16 + 16) >> ls);
-  for (int mt = NT * (w + 4 * blockIdx.z); 16 * mt < K; mt += 4 * NT * gridDim.z) {
+  for (int mt = NT * (w + 4 * blockIdx.z); 16 * mt < K; mt += 4 * NT * parts) {
     v4f acc[NT][4];  // columns 0..15: re, -im; columns 16..31: re, -im
     dense_tiles<NT>(tab, N, K4, mt, lane, [&](int k, float (&x)[4]) {
       const int o = k * kES + (lane & 15);
@@ -161,7 +162,7 @@ __global__ __launch_bounds__(256) void k_dense_rows_r2c(const float* __restrict_
 // as above
 template <int NT, bool PACK>
 __global__ __launch_bounds__(256) void k_dense_rows_c2r(const float2* __restrict__ T, float* __restrict__ f, int ny,
-                                                        int N, int S, int rs, int lsp, float scale,
+                                                        int N, int S, int rs, int lsp, int parts, float scale,
                                                         const float* __restrict__ sub, const float2* __restrict__ tw) {
   extern __shared__ float2 dlds[];
   const int K = N / 2 + 1, K4 = dense_k4(N);
@@ -191,7 +192,7 @@ __global__ __launch_bounds__(256) void k_dense_rows_c2r(const float2* __restrict
   }
   __syncthreads();
   const int c = lane >> 4, l16 = lane & 15, s = s0 + (l16 & sm);
-  for (int it = NT * (w + 4 * blockIdx.z); 16 * it < K; it += 4 * NT * gridDim.z) {
+  for (int it = NT * (w + 4 * blockIdx.z); 16 * it < K; it += 4 * NT * parts) {
     v4f acc[NT][4];  // columns 0..15: cos, sin sums; columns 16..31
     dense_tiles<NT>(tab, N, K4, it, lane, [&](int k, float (&x)[4]) {
       const float2 a = W[k * 16 + (lane & 15)], b = W[(K4 + k) * 16 + (lane & 15)];
@@ -242,7 +243,7 @@ __global__ __launch_bounds__(256) void k_dense_rows_c2r(const float2* __restrict
 template <int DIR, int NT, bool PACK>
 __global__ __launch_bounds__(256) void k_dense_cols(const float2* __restrict__ in, float2* __restrict__ out, int nh,
                                                     int N, int S, int rs, const int32_t* __restrict__ imap,
-                                                    const int32_t* __restrict__ omap, int sfast, int lsp,
+                                                    const int32_t* __restrict__ omap, int sfast, int lsp, int parts,
                                                     const float2* __restrict__ tw) {
   extern __shared__ float2 dlds[];
   const int K = N / 2 + 1, K4 = dense_k4(N);
@@ -292,7 +293,7 @@ __global__ __launch_bounds__(256) void k_dense_cols(const float2* __restrict__ i
   }
   __syncthreads();
   const int c = lane >> 4;  // (the lane's column of the results is col: tid and lane agree in the last four bits)
-  for (int pt = NT * (w + 4 * blockIdx.z); 16 * pt < K; pt += 4 * NT * gridDim.z) {
+  for (int pt = NT * (w + 4 * blockIdx.z); 16 * pt < K; pt += 4 * NT * parts) {
     v4f acc[NT][4];  // C re, S re, C im, S im
     dense_tiles<NT>(tab, N, K4, pt, lane, [&](int k, float (&x)[4]) {
       const float2 e = E[k * 16 + (lane & 15)], o = O[k * 16 + (lane & 15)];
@@ -358,7 +359,7 @@ pat_status dense_rows_r2c(const float* f, float2* T, int ny, int N, int S, int r
   const int ls = slice_bits(S, N, ny, 1), rows = 2 * kDS >> ls;
   dim3 grid((ny + rows - 1) / rows, (S + (1 << ls) - 1) >> ls);
   grid.z = tile_shares(N, grid);
-  auto go = [&](auto kernel) { kernel<<<grid, 256, lds, st>>>(f, T, ny, N, S, rs, ls, tw); };
+  auto go = [&](auto kernel) { kernel<<<grid, 256, lds, st>>>(f, T, ny, N, S, rs, ls, (int)grid.z, tw); };
   if (ls < 4)
     go(k_dense_rows_r2c<1, true>);
   else if (grid.z == 1 && two_tiles(N))
@@ -376,7 +377,7 @@ pat_status dense_rows_c2r(const float2* T, float* f, int ny, int N, int S, int r
   const int ls = slice_bits(S, N, ny, 1), rows = 2 * kDS >> ls;
   dim3 grid((ny + rows - 1) / rows, (S + (1 << ls) - 1) >> ls);
   grid.z = tile_shares(N, grid);
-  auto go = [&](auto kernel) { kernel<<<grid, 256, lds, st>>>(T, f, ny, N, S, rs, ls, scale, sub, tw); };
+  auto go = [&](auto kernel) { kernel<<<grid, 256, lds, st>>>(T, f, ny, N, S, rs, ls, (int)grid.z, scale, sub, tw); };
   if (ls < 4)
     go(k_dense_rows_c2r<1, true>);
   else if (grid.z == 1 && two_tiles(N))
@@ -395,7 +396,7 @@ pat_status dense_cols(int dir, const float2* in, float2* out, int nh, int N, int
   const int sfast = S >= 2048, nsb = (S + (1 << ls) - 1) >> ls, nmb = (nh + per - 1) / per;
   dim3 grid = sfast ? dim3(nsb, nmb) : dim3(nmb, nsb);
   grid.z = tile_shares(N, grid);
-  auto go = [&](auto kernel) { kernel<<<grid, 256, lds, st>>>(in, out, nh, N, S, rs, imap, omap, sfast, ls, tw); };
+  auto go = [&](auto kernel) { kernel<<<grid, 256, lds, st>>>(in, out, nh, N, S, rs, imap, omap, sfast, ls, (int)grid.z, tw); };
   if (ls < 4)
     dir < 0 ? go(k_dense_cols<-1, 1, true>) : go(k_dense_cols<+1, 1, true>);
   else if (grid.z == 1 && two_tiles(N))
