@@ -56,10 +56,14 @@ def reread_bytes(info: dict, adjoint: bool) -> int:
 
 
 def gram_read_info(info: dict, nz: int) -> dict:
-    """info with gram_bytes as one object's Gram product reads them (blocks of
-    up to 128 rows): of every 16 rows the columns from the diagonal on, in
-    whole 32s."""
+    """info with gram_bytes as one object's Gram product reads them: whole
+    blocks, or, where the half-block kernel takes it (up to 64 rows, and up to
+    128 of whole 64 bytes with 1,024 groups of frequencies or more), of every 16
+    rows the columns from the diagonal on, in whole 32s."""
     row = -(-nz // 4) * 4
+    groups = info["read_bytes_A"] * info["nclass"] // info["slab_bytes_A"]
+    if nz > 64 and (nz > 128 or row % 16 or groups < 1024):
+        return info
     half = sum(min(16, nz - 16 * i) * (row - 32 * (i // 2)) for i in range(-(-nz // 16)))
     return dict(info, gram_bytes=info["nclass"] * half * 4)
 
@@ -603,6 +607,8 @@ def forms(op, x, x64, args, samples: dict) -> dict:
         # dense transforms (no fast FFT of 202 points)
         for name, gp in (("invivo_384x326x96x384", Geometry.paper_like(384, 326, 96, 384, dx=50e-6, boundary="linear")),
                          ("wire_202x202x37x256", Geometry.paper_like(202, 202, 37, 256, dx=10e-6, boundary="linear")),
+                         # (the key's name is that of earlier records, whose 202-point
+                         # axes were chirp-z transforms)
                          ("wire_periodic_chirpz_202x202x37x256", Geometry.paper_like(202, 202, 37, 256, dx=10e-6))):
             t0 = time.perf_counter()
             op_ = Operator(gp, "f32")
